@@ -1301,13 +1301,60 @@ __device__ inline void write_record(const ChunkJob& job, uint64_t excl, uint32_t
   if (P > pz) stream::copy_bytes(rec + F + pz, job.slot + job.flag_area + pz, P - pz, lane, 64);
 }
 
-// encode_group writing straight into the final record `rec` (F flag bytes,
-// then the payload): the group's flag bytes are stored one per lane, and only
-// those below F (the payload follows them).
+// Where a chunk's record goes: its F flag bytes and its payload (adjacent in
+// a stream, apart in a scratch slot). ok is false if nothing is to be written.
+struct RecordPlace {
+  uint8_t *flags, *payload;
+  bool ok;
+};
+
+// One record of F flag and P payload bytes, called by the whole workgroup
+// (the sizes are uniform; `shared` is two LDS words that hold nothing else
+// until the next barrier). Single-pass path: wave 0 takes the record's offset
+// from the look-back and writes the table entry (and, for the last chunk, the
+// header, size and status). Two-pass path: the sizes go to job.sizes and the
+// record to the chunk's slot.
+template <bool kSinglePass>
+__device__ __forceinline__ RecordPlace place_record(const ChunkJob& job, uint32_t F, uint32_t P,
+                                                    uint32_t* shared) {
+  RecordPlace r;
+  if constexpr (kSinglePass) {
+    if (threadIdx.x < 64) {
+      const uint64_t excl = lookback(job.desc, job.i, (uint64_t)F + P);
+      if (job.i + 1 == job.N) finish_stream(job, excl, (uint64_t)F + P);
+      const uint64_t te = kHeaderBytes + 8 * job.i;
+      if (threadIdx.x == 0) {
+        if (te + 8 <= job.capacity)
+          *reinterpret_cast<uint64_t*>(job.out + te) = (uint64_t)F | ((uint64_t)P << 32);
+        shared[0] = (uint32_t)excl;
+        shared[1] = (uint32_t)(excl >> 32);
+      }
+    }
+    __syncthreads();
+    const uint64_t excl = (uint64_t)shared[0] | ((uint64_t)shared[1] << 32);
+    const uint64_t rec_off = kHeaderBytes + 8 * job.N + excl;
+    r.ok = excl != kDescValue && rec_off + F + P <= job.capacity;
+    r.flags = job.out + rec_off;
+    r.payload = r.flags + F;
+  } else {
+    if (threadIdx.x == 0) {
+      job.sizes[0] = F;
+      job.sizes[1] = P;
+    }
+    r.ok = true;
+    r.flags = job.slot;
+    r.payload = job.slot + job.flag_area;
+  }
+  return r;
+}
+
+// encode_group writing straight into the record's place: the group's flag
+// bytes are stored one per lane, and only those below F (in a stream the
+// payload follows them).
 template <int S>
 __device__ __forceinline__ void encode_group_out(uint32_t cnt, uint32_t desc, uint32_t group,
-                                                 const typename SymType<S>::T* win, uint8_t* rec,
-                                                 uint32_t F, uint32_t pay) {
+                                                 const typename SymType<S>::T* win,
+                                                 const RecordPlace& rec, uint32_t F, uint32_t pay) {
   using T = typename SymType<S>::T;
   const uint32_t lane = lane_id();
   const bool valid = lane < cnt;
@@ -1315,7 +1362,7 @@ __device__ __forceinline__ void encode_group_out(uint32_t cnt, uint32_t desc, ui
   const uint64_t pm = ballot(is_ptr);
   const uint64_t lm = ballot(valid && !(desc & 1u));
   const uint32_t off = pay + S * mbcnt(lm) + 2u * mbcnt(pm);
-  uint8_t* dst = rec + F + off;
+  uint8_t* dst = rec.payload + off;
   if (is_ptr) {
     dst[0] = (uint8_t)(desc >> 1);
     dst[1] = (uint8_t)(desc >> 9);
@@ -1324,7 +1371,7 @@ __device__ __forceinline__ void encode_group_out(uint32_t cnt, uint32_t desc, ui
 #pragma unroll
     for (int b = 0; b < S; ++b) dst[b] = (uint8_t)((uint64_t)v >> (8 * b));
   }
-  if (lane < 8 && 8u * group + lane < F) rec[8u * group + lane] = (uint8_t)(pm >> (8u * lane));
+  if (lane < 8 && 8u * group + lane < F) rec.flags[8u * group + lane] = (uint8_t)(pm >> (8u * lane));
 }
 
 // Sparse chunks in workgroups of several waves: the exact search at a
@@ -1578,8 +1625,11 @@ __device__ __forceinline__ void bits_range(uint32_t* bm, uint32_t a, uint32_t b,
 // then encodes 64-token groups independently, straight into the record at
 // the offset the look-back gives: a token's position comes from prefix counts
 // of the token bitmap, a group's payload offset from the pointers before it.
-template <int S, int WC>
-__device__ void encode_chunk_spec(const ChunkJob& job, uint8_t* lds) {
+// kStaged: the chunk is in LDS already (a barrier has made it visible).
+// Inlined into every kernel: the generated group loop needs its bounds in
+// scalar registers, which a call would pass in vector ones.
+template <int S, int WC, bool kSinglePass = true, bool kStaged = false>
+__device__ __forceinline__ void encode_chunk_spec(const ChunkJob& job, uint8_t* lds) {
   using T = typename SymType<S>::T;
   constexpr uint32_t kBlock = Geo<S>::kBlock;
   const uint32_t tid = threadIdx.x;
@@ -1601,13 +1651,16 @@ __device__ void encode_chunk_spec(const ChunkJob& job, uint8_t* lds) {
   uint32_t* ends = pc_ptr + tw + 1;
   uint32_t* meet = ends + kSpecWaves;
 
-  stage_chunk<S>(job, stage);
-  for (uint32_t k = tid; k < nhw; k += blockDim.x) hits[k] = 0;
+  if constexpr (!kStaged) stage_chunk<S>(job, stage);
+  // a staged chunk comes here because it is match-dense: every position is a
+  // candidate
+  for (uint32_t k = tid; k < nhw; k += blockDim.x) hits[k] = kStaged ? ~0u : 0u;
   for (uint32_t k = tid; k < 4 * tw; k += blockDim.x) tok[k] = 0;
   __syncthreads();
   const bool sampled = job.MIN >= 2;
-  const uint32_t nblocks = (c + kBlock - 1) / kBlock;
-  if constexpr (Geo<S>::R == 1) {
+  [[maybe_unused]] const uint32_t nblocks = (c + kBlock - 1) / kBlock;
+  if constexpr (kStaged) {
+  } else if constexpr (Geo<S>::R == 1) {
     // fewer blocks than waves: the waves of one block split its window
     // offsets (steps [kb, ke) each) and OR their hits into the bitmap
     constexpr uint32_t V = Geo<S>::V;
@@ -1633,8 +1686,8 @@ __device__ void encode_chunk_spec(const ChunkJob& job, uint8_t* lds) {
   __syncthreads();
   // match-dense chunks (1- and 2-byte symbols, MIN <= 2): at least 1/4 of the
   // tested positions hit; their segments take the streaming parse
-  bool dense = false;
-  if constexpr (kStreamSearch<S>) {
+  bool dense = kStaged && kStreamSearch<S> && job.MIN <= 2;
+  if constexpr (kStreamSearch<S> && !kStaged) {
     if (job.MIN <= 2) {
       if (wave == 0) {
         uint32_t cnt = 0;
@@ -1819,24 +1872,10 @@ __device__ void encode_chunk_spec(const ChunkJob& job, uint8_t* lds) {
   __syncthreads();
   const uint32_t ntok = pc_tok[nbw], nptr = pc_ptr[nbw];
   const uint32_t F = (ntok + 7) / 8, P = S * (ntok - nptr) + 2 * nptr;
-  // ---- record offset (wave 0: look-back), then every wave writes its
-  // groups straight into the record (the join's `ends` words are free now)
-  if (wave == 0) {
-    const uint64_t excl = lookback(job.desc, job.i, (uint64_t)F + P);
-    if (job.i + 1 == job.N) finish_stream(job, excl, (uint64_t)F + P);
-    const uint64_t te = kHeaderBytes + 8 * job.i;
-    if (lane == 0) {
-      if (te + 8 <= job.capacity)
-        *reinterpret_cast<uint64_t*>(job.out + te) = (uint64_t)F | ((uint64_t)P << 32);
-      ends[0] = (uint32_t)excl;
-      ends[1] = (uint32_t)(excl >> 32);
-    }
-  }
-  __syncthreads();
-  const uint64_t excl = (uint64_t)ends[0] | ((uint64_t)ends[1] << 32);
-  const uint64_t rec_off = kHeaderBytes + 8 * job.N + excl;
-  if (excl == kDescValue || rec_off + F + P > job.capacity) return;
-  uint8_t* rec = job.out + rec_off;
+  // ---- record place, then every wave writes its groups straight into it (the
+  // join's `ends` words are free now)
+  const RecordPlace rec = place_record<kSinglePass>(job, F, P, ends);
+  if (!rec.ok) return;
   const uint32_t groups = (ntok + 63) / 64;
   for (uint32_t g = wave; g < groups; g += nwaves) {
     const uint32_t r = 64 * g + lane;  // this lane's token rank

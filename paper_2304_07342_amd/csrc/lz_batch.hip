@@ -19,7 +19,7 @@
 // chunk counts and record-offset groups, one workgroup per buffer for its
 // table, then a persistent decoder over all chunks.
 #include "decode_device.h"
-#include "encode_device.h"
+#include "bucket_device.h"
 #include "stream_device.h"
 
 namespace gpulz {
@@ -137,7 +137,8 @@ __global__ __launch_bounds__(kPlanThreads) void batch_enc_plan_kernel(BatchEncAr
   }
 }
 
-template <int S, int WC>
+// kBucket: the bucket encoder with 256 threads.
+template <int S, int WC, bool kBucket>
 __device__ __forceinline__ void encode_item(const BatchEncArgs& a, uint64_t b, const BatchEncBuf& e,
                                             uint64_t i, uint8_t* lds) {
   const uint64_t cs = i * e.C;
@@ -151,14 +152,15 @@ __device__ __forceinline__ void encode_item(const BatchEncArgs& a, uint64_t b, c
   job.slot = a.slots + e.slot_base + i * e.slot_bytes;
   job.flag_area = e.flag_area;
   job.sizes = a.sizes + 2 * (e.chunk_base + i);
-  enc::encode_chunk<S, WC>(job, lds);
+  if constexpr (kBucket) enc::bucket::encode_chunk<S, WC, 256, false>(job, lds);
+  else enc::encode_chunk<S, WC>(job, lds);
 }
 
 // Persistent encoder for the chunks of symbol width S (width index WI); the
 // window spans WC columns of 64 offsets (one window per width in a batch).
 // At least 6 waves per SIMD: the 1-byte encoder then fits in 80 VGPRs (82
 // otherwise, 5 waves) without spilling; the other widths need fewer.
-template <int S, uint32_t WI, int WC>
+template <int S, uint32_t WI, int WC, bool kBucket>
 __global__ __launch_bounds__(64 * enc::kEncodeWaves) __attribute__((amdgpu_waves_per_eu(6)))
 void batch_encode_kernel(BatchEncArgs a) {
   extern __shared__ __align__(16) uint8_t lds[];
@@ -173,7 +175,7 @@ void batch_encode_kernel(BatchEncArgs a) {
     if (g >= T) break;
     const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].width_base[WI]; });
     const BatchEncBuf& e = a.bufs[b];
-    encode_item<S, WC>(a, b, e, g - e.width_base[WI], lds);
+    encode_item<S, WC, kBucket>(a, b, e, g - e.width_base[WI], lds);
     __syncthreads();
   }
 }
@@ -332,18 +334,30 @@ int device_cus() {
 
 }  // namespace
 
-template <int S, uint32_t WI, int WC>
-hipError_t launch_width_wc(const BatchEncArgs& a, hipStream_t s) {
-  const uint32_t threads = 64 * a.wp.waves[WI];
-  const size_t lds = encode_lds_bytes(a.wp.C[WI], S, a.wp.W[WI], a.wp.waves[WI]);
+template <int S, uint32_t WI, int WC, bool kBucket>
+hipError_t launch_persistent(const BatchEncArgs& a, uint32_t threads, size_t lds, hipStream_t s) {
   int per_cu = 0;
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, batch_encode_kernel<S, WI, WC>, threads, lds);
+      &per_cu, batch_encode_kernel<S, WI, WC, kBucket>, threads, lds);
   if (err != hipSuccess) return err;
   if (per_cu < 1) per_cu = 1;
-  hipLaunchKernelGGL((batch_encode_kernel<S, WI, WC>), dim3(device_cus() * per_cu), dim3(threads),
-                     lds, s, a);
+  hipLaunchKernelGGL((batch_encode_kernel<S, WI, WC, kBucket>), dim3(device_cus() * per_cu),
+                     dim3(threads), lds, s, a);
   return hipGetLastError();
+}
+
+template <int S, uint32_t WI, int WC>
+hipError_t launch_width_wc(const BatchEncArgs& a, hipStream_t s) {
+  const uint32_t C = a.wp.C[WI];
+  if constexpr (S <= 2) {
+    constexpr int WF = enc::bucket::kFallbackWC<S, WC>;
+    const size_t lds = enc::bucket::chunk_lds<S, WF>(C, a.wp.W[WI], 256);
+    if (enc::bucket::takes(C, a.wp.MIN[WI], lds))
+      return launch_persistent<S, WI, WF, true>(a, 256, lds, s);
+  }
+  const uint32_t waves = a.wp.waves[WI];
+  return launch_persistent<S, WI, WC, false>(a, 64 * waves,
+                                             encode_lds_bytes(C, S, a.wp.W[WI], waves), s);
 }
 
 template <int S, uint32_t WI>

@@ -4,7 +4,7 @@
 // find their record offsets by decoupled look-back and write the table entry
 // and record straight into the stream. Match policy 0 (exact longest match)
 // and 1 (the paper's single window pass).
-#include "encode_device.h"
+#include "bucket_device.h"
 
 namespace gpulz {
 namespace {
@@ -14,6 +14,9 @@ namespace {
 // 512 for 4-byte ones).
 constexpr uint64_t kSpecMaxChunksNarrow = 1024;  // S <= 2
 constexpr uint64_t kSpecMaxChunksWide = 512;     // S >= 4
+// Launches of at most this many chunks take the bucket encoder with 16 waves
+// per chunk instead of 4.
+constexpr uint64_t kBucketFewChunks = 512;
 
 __global__ __launch_bounds__(256) void prep_kernel(FusedArgs a) {
   const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -87,6 +90,17 @@ __global__ __launch_bounds__(64 * enc::kSpecWaves) void encode_spec_kernel(Fused
   enc::encode_chunk_spec<S, WC>(job, lds);
 }
 
+// 1- and 2-byte symbols with MIN >= 2: candidates from 2-symbol buckets, NT
+// threads per chunk (see bucket_device.h).
+template <int S, int WC, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6)))
+void encode_bucket_kernel(FusedArgs a) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ uint64_t item;
+  const enc::ChunkJob job = take_chunk(a, S, &item);
+  enc::bucket::encode_chunk<S, WC, NT, true>(job, lds);
+}
+
 // Policy-1 chunk encoder kernel: one workgroup per chunk.
 template <int S>
 __global__ __launch_bounds__(64 * enc::kEncodeWaves) void encode_scan_kernel(FusedArgs a) {
@@ -98,6 +112,20 @@ __global__ __launch_bounds__(64 * enc::kEncodeWaves) void encode_scan_kernel(Fus
 
 template <int S, int WC>
 hipError_t launch_sw(const FusedArgs& a, uint32_t waves, hipStream_t s) {
+  if constexpr (S <= 2) {
+    constexpr int WF = enc::bucket::kFallbackWC<S, WC>;
+    constexpr uint32_t kNT = 256;
+    const uint32_t threads = a.N <= kBucketFewChunks ? 1024 : kNT;
+    const size_t lds = enc::bucket::chunk_lds<S, WF>(a.C, a.W, threads);
+    if (enc::bucket::takes(a.C, a.MIN, lds)) {
+      const dim3 grid((uint32_t)a.nchunks), block(threads);
+      if (threads == 1024)
+        hipLaunchKernelGGL((encode_bucket_kernel<S, WF, 1024>), grid, block, lds, s, a);
+      else
+        hipLaunchKernelGGL((encode_bucket_kernel<S, WF, kNT>), grid, block, lds, s, a);
+      return hipGetLastError();
+    }
+  }
   const size_t spec_lds = enc::spec_lds_bytes<S, WC>(a.C);
   const uint64_t spec_max = S <= 2 ? kSpecMaxChunksNarrow : kSpecMaxChunksWide;
   if (a.N <= spec_max && a.C <= enc::kSpecMaxSyms && spec_lds <= kMaxGroupLdsBytes) {
