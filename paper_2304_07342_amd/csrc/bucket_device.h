@@ -96,9 +96,13 @@ __host__ __device__ constexpr uint64_t chunk_lds(uint32_t C, uint32_t W, uint32_
 // Window columns of that split parse for a window of wc columns: one variant
 // for bytes, two for 2-byte symbols (one or two streaming columns).
 template <int S, int WC> constexpr int kFallbackWC = S == 2 && WC <= 2 ? 2 : 4;
-// Whether this encoder takes chunks of C symbols with these parameters.
-__host__ constexpr bool takes(uint32_t C, uint32_t MIN, uint64_t lds) {
-  return MIN >= 2 && C <= kMaxSyms && lds <= kMaxGroupLdsBytes;
+// Whether this encoder takes chunks of C symbols with these parameters: MIN = 2,
+// and larger MIN where the split parse would be the other choice (`few`).
+// MIN = 1 needs single symbols as candidates; one-wave encoders with larger MIN
+// keep their own parse.
+__host__ constexpr bool takes(uint32_t C, uint32_t MIN, uint64_t lds, bool few) {
+  return (MIN == 2 || (MIN > 2 && few && C <= kSpecMaxSyms)) && C <= kMaxSyms &&
+         lds <= kMaxGroupLdsBytes;
 }
 
 __device__ __forceinline__ uint32_t hash2(uint32_t x) {
@@ -156,11 +160,13 @@ __device__ __forceinline__ bool take_low_bytes(const uint8_t* stage, uint32_t c,
 
 // The longest match of every position of the chunk into res (all waves).
 // sym holds the symbols as bytes; exact: equal bytes mean equal symbols, else
-// results are checked in the staged 2-byte symbols. Returns false, uniformly,
-// if a tile's buckets are so full that comparing every position with its
-// window is cheaper (long runs of few symbols).
+// results are checked in the staged 2-byte symbols. Returns kSearched, or,
+// uniformly, that a tile's buckets are so full that comparing every position
+// with its window is cheaper (runs of few symbols: kFull) or that most of its
+// positions have the same two symbols (kConstant).
+enum SearchEnd { kSearched, kFull, kConstant };
 template <int S, int NT>
-__device__ __forceinline__ bool search(const uint8_t* stage, const uint8_t* sym, bool exact,
+__device__ __forceinline__ SearchEnd search(const uint8_t* stage, const uint8_t* sym, bool exact,
                                        uint32_t c, uint32_t W, uint32_t MIN, uint16_t* res,
                                        uint2* order, uint32_t* cnt32, uint32_t* shared,
                                        uint32_t seg_sh) {
@@ -199,7 +205,11 @@ __device__ __forceinline__ bool search(const uint8_t* stage, const uint8_t* sym,
     ranks = readlane(wave_incl_scan(ranks), 63);
     if (lane == 0) atomicAdd(&shared[kMaxWaves], ranks);
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(shared[kMaxWaves]) > 8 * n) return false;
+    // n positions of equal share among k buckets of a block have a mean rank of
+    // kPB / 2k: full buckets hold more than about 16 entries per block, and
+    // above 48 (of at most 63.5) one bucket holds nearly all
+    ranks = __builtin_amdgcn_readfirstlane(shared[kMaxWaves]);
+    if (ranks > 8 * n) return ranks > 48 * n ? kConstant : kFull;
     // exclusive scan of the counters, in place: one hash per thread, the
     // hashes with more than 24 entries first, then those with more than 8
     uint32_t wv[kMaxRow], sum = 0;
@@ -289,7 +299,7 @@ __device__ __forceinline__ bool search(const uint8_t* stage, const uint8_t* sym,
     if (t0 + kTile >= c && tid == 0) res[res_at(c - 1, seg_sh)] = 0;
     __syncthreads();
   }
-  return true;
+  return kSearched;
 }
 
 // Greedy parse from LDS results: lane g of the workgroup takes segment g. All segments are parsed at once, each as if a token started
@@ -409,10 +419,11 @@ __device__ __forceinline__ void encode_chunk(const ChunkJob& job, uint8_t* lds) 
   __syncthreads();
   bool exact = true;
   if constexpr (S == 2) exact = take_low_bytes<NT>(stage, c, low, shared);
-  if (!search<S, NT>(stage, S == 2 ? low : stage, exact, c, job.W, job.MIN, res, order, cnt32,
-                     shared, seg_sh)) {
+  const SearchEnd end = search<S, NT>(stage, S == 2 ? low : stage, exact, c, job.W, job.MIN, res,
+                                      order, cnt32, shared, seg_sh);
+  if (end != kSearched) {
     __syncthreads();
-    encode_chunk_spec<S, WC, kSinglePass, true>(job, lds);
+    encode_chunk_spec<S, WC, kSinglePass, true>(job, lds, end == kConstant);
     return;
   }
 

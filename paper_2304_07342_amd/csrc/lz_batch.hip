@@ -352,7 +352,7 @@ hipError_t launch_width_wc(const BatchEncArgs& a, hipStream_t s) {
   if constexpr (S <= 2) {
     constexpr int WF = enc::bucket::kFallbackWC<S, WC>;
     const size_t lds = enc::bucket::chunk_lds<S, WF>(C, a.wp.W[WI], 256);
-    if (enc::bucket::takes(C, a.wp.MIN[WI], lds))
+    if (enc::bucket::takes(C, a.wp.MIN[WI], lds, false))
       return launch_persistent<S, WI, WF, true>(a, 256, lds, s);
   }
   const uint32_t waves = a.wp.waves[WI];

@@ -49,7 +49,7 @@ SIZES = [1, 2, 15, 63, 1023, 1024, 1025, 1026, 1300, 2047, 2050, 4097, 8191, 819
 @pytest.mark.parametrize("C", SIZES)
 def test_chunk_sizes(S, C):
     for k, W in enumerate((1, 2, 127, 128, 129, 256)):
-        for MIN in (2, 3, 6, 7):
+        for MIN in (2, 3, 6, 7) if C <= 4096 else (2,):
             x = repeats(2 * C + C // 3, S, 31 * C + 8 * k + MIN, 9 if k % 2 else 60)
             print("bucket", S, C, W, MIN, x.size, flush=True)
             st, s, _, canary = gpu_compress(x, S, C, W, MIN)
