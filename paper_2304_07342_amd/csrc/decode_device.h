@@ -8,8 +8,17 @@
 //            chunks (one u64 per group; the sum must end exactly at the
 //            stream's end); a chunk's record offset is its group's offset
 //            plus a 64-lane prefix sum over the group's table entries;
-//   chunk    (chunks of at most 4096 symbols and 16 KiB, the usual case) one
-//            workgroup of 256 threads per chunk: the record is staged into
+//   chunk    (1- and 2-byte symbols, many chunks) one wavefront per chunk walks the tokens 64
+//            at a time: lane l takes token t + l, its flag bit gives its kind,
+//            mbcnt over the literal / pointer ballots its payload offset, a
+//            wave scan of the token lengths its output position. Literals are
+//            written into an LDS ring of recent symbols; then the new symbols
+//            are taken 64 at a time, one per lane: a pointer's symbol follows
+//            its source back to a literal or out of the 64, in registers, and
+//            copies it. Finished symbols stream out to HBM; the next tokens'
+//            payload is loaded meanwhile;
+//   chunk    (4- and 8-byte symbols, or few chunks; at most 4096 symbols and
+//            16 KiB) one workgroup of 256 threads per chunk: the record is staged into
 //            LDS with 16-byte loads; block-wide scans over the flag bits and
 //            the token lengths give every token's payload offset and output
 //            position at once, every rule is checked and the literals are
@@ -39,39 +48,40 @@ namespace dec {
 
 constexpr uint32_t kGroup = 64;  // chunks per record-offset group
 
-__device__ inline uint64_t rd_u64(const uint8_t* p) {
-  uint64_t v = 0;
-  for (int k = 7; k >= 0; --k) v = (v << 8) | p[k];
-  return v;
-}
-__device__ inline uint32_t rd_u32(const uint8_t* p) {
-  return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
-}
-
-// Checks the header of a stream of in_bytes bytes; fills p (p.status = kOk or
-// kCorrupt). One thread.
+// Checks the header of a stream of in_bytes bytes (16-byte aligned, as every
+// entry point requires); fills p (p.status = kOk or kCorrupt). One thread; the
+// header is four 16-byte loads in flight together, its fields register words.
 __device__ inline void parse_header(const uint8_t* h, uint64_t in_bytes, DecodeParams& p) {
   p = DecodeParams{};
   bool ok = in_bytes >= kHeaderBytes;
   if (ok) {
-    ok = h[0] == 'G' && h[1] == 'L' && h[2] == 'Z' && h[3] == '1' && h[4] == 1 && h[5] == 0 &&
-         h[7] <= 1 && h[15] == kMaxMatch;  // match policy 0 or 1
-    p.S = h[6];
-    p.C = rd_u32(h + 8);
-    p.W = (uint32_t)h[12] | ((uint32_t)h[13] << 8);
-    p.MIN = h[14];
-    p.n = rd_u64(h + 16);
-    p.N = rd_u64(h + 24);
-    const uint64_t total = rd_u64(h + 32);
-    p.r = h[40];
+    uint4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = reinterpret_cast<const uint4*>(h)[k];
+    const uint32_t w[16] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w,
+                            v[2].x, v[2].y, v[2].z, v[2].w, v[3].x, v[3].y, v[3].z, v[3].w};
+    ok = w[0] == 0x315A4C47u &&            // "GLZ1"
+         (w[1] & 0xFFFFu) == 1u &&         // version
+         w[1] >> 24 <= 1u &&               // match policy 0 or 1
+         w[3] >> 24 == kMaxMatch;
+    p.S = w[1] >> 16 & 0xFFu;
+    p.C = w[2];
+    p.W = w[3] & 0xFFFFu;
+    p.MIN = w[3] >> 16 & 0xFFu;
+    p.n = (uint64_t)w[5] << 32 | w[4];
+    p.N = (uint64_t)w[7] << 32 | w[6];
+    const uint64_t total = (uint64_t)w[9] << 32 | w[8];
+    p.r = w[10] & 0xFFu;
     ok = ok && (p.S == 1 || p.S == 2 || p.S == 4 || p.S == 8) && p.C >= 1 && p.C <= (1u << 24) &&
          p.W >= 1 && p.W <= kMaxWindow && p.MIN >= 1;
     if (ok) {
       p.m = p.n / p.S;
       ok = p.r == p.n % p.S && p.N == (p.m + p.C - 1) / p.C && total == in_bytes &&
            p.N <= decode_max_chunks(in_bytes);
-      for (uint32_t k = 41; k < 48; ++k) ok = ok && h[k] == 0;
-      for (uint32_t k = 48 + p.r; k < 64; ++k) ok = ok && h[k] == 0;
+      // bytes 41..47 are zero, and those of 48..63 past the r tail bytes
+      const uint64_t tail = (uint64_t)w[13] << 32 | w[12];
+      ok = ok && w[10] >> 8 == 0 && w[11] == 0 && w[14] == 0 && w[15] == 0 &&
+           (p.r >= 8 || tail >> (8 * p.r) == 0);
     }
   }
   p.status = ok ? kOk : kCorrupt;
@@ -199,6 +209,165 @@ __device__ bool decode_chunk(const uint8_t* flags, uint32_t F, uint32_t P, uint3
   if ((t + 7) / 8 != F || u != P) return false;
   if (t < 8ull * F && (flags[F - 1] >> (uint32_t)(t - 8ull * (F - 1))) != 0) return false;
   return true;
+}
+
+// ---- wave decoder of 1- and 2-byte symbols ---------------------------------
+
+constexpr uint32_t kRingSyms = 1024;  // symbols of a wave's ring
+constexpr uint32_t kFlushSyms = 256;  // symbols written out at once
+// Symbols a step may add, up to 254 more for the last token's end: what is not
+// written out yet (below kFlushSyms) or may be a source (the last 256) and the
+// new ones fit the ring.
+constexpr uint32_t kSpanSyms = kRingSyms - kFlushSyms - kMaxMatch - 1;
+constexpr uint32_t kStepSyms = kSpanSyms + 256;  // symbols of a step, at most
+constexpr uint32_t kShortFill = 8;  // longer pointers' offsets are laid out by all lanes
+template <int S> struct WaveLds {
+  typename SymType<S>::T ring[kRingSyms];
+  uint16_t off[kStepSyms];  // offset of each new symbol's pointer, 0 for a literal
+};
+
+// 8 bytes of [p, end) from byte 8 k on (zeros past the end), any alignment.
+__device__ __forceinline__ uint64_t load_bytes8(const uint8_t* p, uint32_t k, uint32_t n) {
+  uint64_t v = 0;
+  if (8 * k + 8 <= n) {
+    __builtin_memcpy(&v, p + 8 * k, 8);
+  } else {
+    for (uint32_t b = 8 * k; b < n; ++b) v |= (uint64_t)p[b] << (8 * (b - 8 * k));
+  }
+  return v;
+}
+
+// Decode one chunk of c symbols with one wavefront; returns false (uniformly)
+// if it breaks a rule. `flags` is the record (F flag bytes, then P payload
+// bytes; no byte past them is read).
+template <int S>
+__device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, uint32_t c,
+                                  uint32_t W, uint32_t MIN, typename SymType<S>::T* out,
+                                  WaveLds<S>& lds) {
+  using T = typename SymType<S>::T;
+  using Quad = typename SymType<4 * S>::T;
+  T* const ring = lds.ring;
+  static_assert(S <= 2, "a token's payload is at most two bytes");
+  constexpr uint32_t M = kRingSyms - 1;
+  const uint32_t lane = lane_id();
+  if (F > (c + 7) / 8) return false;  // more tokens than symbols
+  const uint8_t* pay = flags + F;
+  const bool wide = ((uintptr_t)out & 15u) == 0;
+  const uint32_t rounds = (F + 7) / 8;
+  uint32_t q = 0;        // symbols decoded
+  uint32_t done = 0;     // symbols written out
+  uint32_t t = 0, u = 0;  // tokens taken, their payload bytes
+  uint64_t fw = 0;       // flag words of 64 rounds, one per lane
+
+  // this lane's payload (2 bytes, or 1 at the payload's end) at offset `off`
+  auto payload = [&](bool has, uint32_t off) -> uint32_t {
+    uint32_t v = 0;
+    if (has && off + 2 <= P) {
+      uint16_t x;
+      __builtin_memcpy(&x, pay + off, 2);
+      v = x;
+    } else if (S == 1 && has && off < P) {
+      v = pay[off];
+    }
+    return v;
+  };
+  auto flush = [&](uint32_t n) {  // writes out symbols [done, done + n)
+    if (wide && n == kFlushSyms) {  // four symbols per lane
+      reinterpret_cast<Quad*>(out + done)[lane] = reinterpret_cast<const Quad*>(ring + (done & M))[lane];
+    } else {
+      for (uint32_t k = lane; k < n; k += 64) out[done + k] = ring[(done + k) & M];
+    }
+    done += n;
+  };
+
+  uint64_t pm_next = 0;
+  uint32_t v_next = 0, off_next = 0, u_next = 0;
+  for (uint32_t r = 0; r <= rounds; ++r) {
+    const uint64_t pm = pm_next;
+    const uint32_t v = v_next, off = off_next;
+    const uint32_t base = 64 * (r - 1);  // this round's first token (r >= 1)
+    if (r < rounds) {  // the next round's flags and payload
+      if ((r & 63u) == 0) fw = 8 * (r + lane) < F ? load_bytes8(flags, r + lane, F) : 0ull;
+      pm_next = (uint64_t)readlane((uint32_t)(fw >> 32), r & 63u) << 32 |
+                readlane((uint32_t)fw, r & 63u);
+      const uint32_t left = 8 * F - 64 * r;  // tokens the flags can still describe
+      const uint64_t hm = left >= 64 ? ~0ull : (1ull << left) - 1ull;
+      const uint64_t lm = hm & ~pm_next;
+      off_next = u_next + S * mbcnt(lm) + 2u * mbcnt(pm_next);
+      v_next = payload(hm >> lane & 1, off_next);
+      u_next += S * popc64(lm) + 2u * popc64(pm_next);
+    }
+    if (r == 0) continue;
+
+    const uint32_t left = 8 * F - base;
+    const bool has = lane < left;
+    const bool ptr = pm >> lane & 1;
+    const uint32_t sz = ptr ? 2u : (uint32_t)S;
+    const uint32_t L = ptr ? v & 0xFFu : 1u;
+    const uint32_t O = ptr ? ((v >> 8) - 1u & 0xFFu) + 1u : 1u;
+    const uint32_t len = has ? L : 0u;
+    const uint32_t incl = wave_incl_scan(len);
+    const uint32_t pos = q + incl - len;
+    const uint32_t total = readlane(incl, 63);
+    const uint64_t tm = ballot(has && pos < c);  // tokens of the chunk (a prefix)
+    bool bad = off + sz > P;
+    if (ptr) bad = bad || L < MIN || O > W || O > pos || L > O || pos + L > c;
+    if (ballot((tm >> lane & 1) && bad)) return false;
+    if (tm == 0) break;  // the chunk was complete before this round
+    // usually one step; a round of long pointers takes several
+    uint64_t todo = tm;
+    for (;;) {
+      uint64_t now = todo;
+      if (total > kSpanSyms) now = ballot((todo >> lane & 1) && pos < q + kSpanSyms);
+      const bool mine = now >> lane & 1;
+      const uint32_t at = pos - q;
+      if (mine) lds.off[at] = (uint16_t)(ptr ? O : 0u);
+      if (mine && !ptr) ring[pos & M] = (T)v;
+      const bool fill = mine && ptr;
+      for (uint32_t k = 1; ballot(fill && L <= kShortFill && k < L); ++k)
+        if (fill && L <= kShortFill && k < L) lds.off[at + k] = (uint16_t)O;
+      uint64_t big = ballot(fill && L > kShortFill);
+      while (big) {
+        const uint32_t j = (uint32_t)__builtin_ctzll(big);
+        big &= big - 1;
+        const uint32_t aj = readlane(at, j), Lj = readlane(L, j), Oj = readlane(O, j);
+        for (uint32_t k = lane; k < Lj; k += 64) lds.off[aj + k] = (uint16_t)Oj;
+      }
+      wave_sync();
+      const uint32_t last = 63u - (uint32_t)__builtin_clzll(now);
+      const uint32_t n = readlane(pos + len, last) - q;  // new symbols
+      for (uint32_t b = 0; b < n; b += 64) {
+        // sources relative to this lane's 64 symbols: negative ones are final,
+        // a literal is its own source; each step replaces a source by its
+        // source's source, so a chain of 64 ends after 6
+        const uint32_t p = q + b + lane;
+        const uint32_t o = b + lane < n ? lds.off[b + lane] : 0u;
+        int32_t s = (int32_t)(lane - o);
+        for (;;) {
+          const int32_t s2 = __builtin_amdgcn_ds_bpermute(4 * s, s);
+          const bool on = s >= 0 && s2 != s;
+          if (!ballot(on)) break;
+          s = on ? s2 : s;
+        }
+        const T x = ring[(q + b + (uint32_t)s) & M];
+        if (o) ring[p & M] = x;
+        wave_sync();
+      }
+      todo &= ~now;
+      q += n;
+      while (q - done >= kFlushSyms) flush(kFlushSyms);
+      if (!todo) break;
+    }
+    t += popc64(tm);
+    u += S * popc64(tm & ~pm) + 2u * popc64(tm & pm);
+    if (q >= c) break;
+  }
+  if (q < c) return false;  // flags exhausted before the chunk is complete
+  wave_sync();
+  flush(c - done);
+  wave_sync();
+  if ((t + 7) / 8 != F || u != P) return false;
+  return t == 8 * F || flags[F - 1] >> (t - 8 * (F - 1)) == 0;
 }
 
 // ---- workgroup decoder ------------------------------------------------------
@@ -636,6 +805,48 @@ __device__ inline bool copy_literal_chunk(const uint8_t* rec, const uint8_t* in_
   }
   for (uint32_t b = 16 * ng + tid; b < nb; b += kDecThreads) dst[b] = src[b];
   return true;
+}
+
+// A wave-uniform value in a scalar register.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
+}
+
+// Where chunk i of a validated stream is and goes (all wave-uniform).
+struct ChunkPlace {
+  const uint8_t* rec;
+  uint32_t F, P, c;
+  uint8_t* dst;
+};
+__device__ inline ChunkPlace chunk_place(const uint8_t* in, const DecodeParams& p,
+                                         const uint64_t* group_off, uint64_t i, uint8_t* out) {
+  ChunkPlace k;
+  i = uniform(i);
+  const uint8_t* e = in + kHeaderBytes + 8 * i;
+  k.F = uniform(*reinterpret_cast<const uint32_t*>(e));
+  k.P = uniform(*reinterpret_cast<const uint32_t*>(e + 4));
+  k.rec = in + uniform(record_offset(in, group_off, i));
+  const uint64_t cs = i * p.C;
+  k.c = (uint32_t)min<uint64_t>(p.C, p.m - cs);
+  k.dst = out + cs * p.S;
+  return k;
+}
+
+// LDS of one wave of decode_stream_chunk_wave.
+constexpr uint32_t kWaveLds = (sizeof(WaveLds<2>) + 15) / 16 * 16;
+
+// Decode chunk i of a validated stream of 1- or 2-byte symbols with one
+// wavefront and kWaveLds bytes of LDS; false (uniformly) if it is corrupt.
+__device__ inline bool decode_stream_chunk_wave(const uint8_t* in, const DecodeParams& p,
+                                                const uint64_t* group_off, uint64_t i,
+                                                uint8_t* out, uint8_t* lds) {
+  const ChunkPlace k = chunk_place(in, p, group_off, i, out);
+  const uint32_t F = k.F, P = k.P, c = k.c;
+  if (p.S == 1)
+    return decode_chunk_wave<1>(k.rec, F, P, c, p.W, p.MIN, k.dst, *reinterpret_cast<WaveLds<1>*>(lds));
+  return decode_chunk_wave<2>(k.rec, F, P, c, p.W, p.MIN, reinterpret_cast<uint16_t*>(k.dst),
+                              *reinterpret_cast<WaveLds<2>*>(lds));
 }
 
 // Decode chunk i of a validated stream of in_bytes bytes with the whole

@@ -305,17 +305,42 @@ __global__ __launch_bounds__(256) void batch_dec_table_kernel(BatchDecArgs a) {
   }
 }
 
+// Batches of more chunks than this have those of 1- and 2-byte symbols decoded
+// by one wave per chunk (see lz_decode.hip).
+constexpr uint64_t kFewBatchChunks = 1536;
+__device__ __forceinline__ bool narrow_by_waves(const BatchDecArgs& a) {
+  return a.ctrl->T_all > kFewBatchChunks;
+}
+
 __global__ __launch_bounds__(dec::kDecThreads, 4) void batch_decode_kernel(BatchDecArgs a) {
   __shared__ __align__(16) dec::BlockLds sm;
   const uint64_t T = a.ctrl->T_all;
   for (uint64_t g = blockIdx.x; g < T; g += gridDim.x) {
     const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].chunk_base; });
     const BatchDecBuf& e = a.bufs[b];
-    if (e.p.status != kOk) continue;
+    if (e.p.status != kOk || (e.p.S <= 2 && narrow_by_waves(a))) continue;
     const bool ok = dec::decode_stream_chunk_block(
         static_cast<const uint8_t*>(a.in_ptrs[b]), a.in_bytes[b], e.p, a.group_off + e.group_base,
         g - e.chunk_base, static_cast<uint8_t*>(a.out_ptrs[b]), sm);
     if (!ok && threadIdx.x == 0) atomicExch(&a.status[b], kCorrupt);
+  }
+}
+
+constexpr uint32_t kWaveThreads = 1024;
+
+__global__ __launch_bounds__(kWaveThreads, 8) void batch_decode_wave_kernel(BatchDecArgs a) {
+  __shared__ __align__(16) uint8_t lds[kWaveThreads / 64 * dec::kWaveLds];
+  if (!narrow_by_waves(a)) return;
+  const uint32_t wave = dec::uniform(threadIdx.x >> 6);
+  const uint64_t T = a.ctrl->T_all, waves = (uint64_t)gridDim.x * (kWaveThreads / 64);
+  for (uint64_t g = blockIdx.x + (uint64_t)wave * gridDim.x; g < T; g += waves) {
+    const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].chunk_base; });
+    const BatchDecBuf& e = a.bufs[b];
+    if (e.p.status != kOk || e.p.S > 2) continue;
+    const bool ok = dec::decode_stream_chunk_wave(
+        static_cast<const uint8_t*>(a.in_ptrs[b]), e.p, a.group_off + e.group_base, g - e.chunk_base,
+        static_cast<uint8_t*>(a.out_ptrs[b]), lds + wave * dec::kWaveLds);
+    if (!ok && lane_id() == 0) atomicExch(&a.status[b], kCorrupt);
   }
 }
 
@@ -396,6 +421,8 @@ hipError_t launch_decompress_batch(const BatchDecArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(batch_dec_table_kernel, dim3((uint32_t)a.nbufs), dim3(256), 0, s, a);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(batch_decode_kernel, dim3(device_cus() * 4), dim3(dec::kDecThreads), 0, s, a);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  hipLaunchKernelGGL(batch_decode_wave_kernel, dim3(device_cus() * 2), dim3(kWaveThreads), 0, s, a);
   return hipGetLastError();
 }
 
