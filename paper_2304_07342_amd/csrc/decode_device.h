@@ -41,6 +41,7 @@
 #pragma once
 
 #include "gpulz_internal.h"
+#include "stream_device.h"
 #include "wave.h"
 
 namespace gpulz {
@@ -739,26 +740,6 @@ __device__ bool decode_chunk_block(const uint8_t* rec, const uint8_t* in_end, ui
   return true;
 }
 
-// 16 bytes starting sh bytes (0..3) past the dword at q (global memory),
-// funnel-shifted from dword reads that never reach in_end.
-__device__ __forceinline__ uint4 load_group(const uint32_t* q, uint32_t sh, const uint8_t* in_end) {
-  uint32_t d[5];
-  __builtin_memcpy(d, __builtin_assume_aligned(q, 4), 16);
-  d[4] = 0;
-  if (sh) {
-    // the fifth dword holds the group's last sh bytes; at the end of the
-    // stream it is read byte by byte
-    const uint8_t* q4 = reinterpret_cast<const uint8_t*>(q + 4);
-    if (q4 + 4 <= in_end) {
-      d[4] = q[4];
-    } else {
-      for (uint32_t b = 0; b < sh; ++b) d[4] |= (uint32_t)q4[b] << (8 * b);
-    }
-  }
-  return make_uint4(__builtin_amdgcn_alignbyte(d[1], d[0], sh), __builtin_amdgcn_alignbyte(d[2], d[1], sh),
-                    __builtin_amdgcn_alignbyte(d[3], d[2], sh), __builtin_amdgcn_alignbyte(d[4], d[3], sh));
-}
-
 // A record sized for c literals (F = ceil(c / 8) flag bytes, P = c S payload
 // bytes) whose flag bytes are all zero is valid and its payload is the chunk:
 // copy it straight from the stream to the output (dword-aligned 16-byte loads,
@@ -795,7 +776,7 @@ __device__ inline bool copy_literal_chunk(const uint8_t* rec, const uint8_t* in_
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j) {
       const uint32_t k = k0 + j * kDecThreads;
-      if (k < ng) g[j] = load_group(sw + 4 * k, sh, in_end);
+      if (k < ng) g[j] = stream::load_group(sw + 4 * k, sh, in_end);
     }
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j) {
@@ -805,12 +786,6 @@ __device__ inline bool copy_literal_chunk(const uint8_t* rec, const uint8_t* in_
   }
   for (uint32_t b = 16 * ng + tid; b < nb; b += kDecThreads) dst[b] = src[b];
   return true;
-}
-
-// A wave-uniform value in a scalar register.
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint64_t uniform(uint64_t v) {
-  return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
 }
 
 // Where chunk i of a validated stream is and goes (all wave-uniform).

@@ -1188,56 +1188,69 @@ __device__ __forceinline__ uint64_t desc_load(const uint64_t* p) {
 constexpr uint32_t kLookbackPolls = 1u << 22;
 constexpr uint32_t kNoGroup = 0xFFFFFFFFu;
 
-// One wavefront, all lanes: publishes chunk i's record bytes `agg`, sums the
-// record bytes of chunks 0..i-1 from their descriptors, 64 per round, back to
-// the nearest inclusive prefix, publishes chunk i's inclusive prefix and
-// returns the exclusive one (the record's offset past the table). Chunk ids
-// follow the order of an atomic ticket taken when a workgroup starts, so
-// every predecessor belongs to a running or finished workgroup, which
-// publishes its size right after its own parse: every wait ends. As a guard
+// One lane: publishes chunk i's record bytes `agg`.
+__device__ __forceinline__ void publish(uint64_t* desc, uint64_t i, uint64_t agg) {
+  if (lane_id() == 0) desc_store(desc + i, (i == 0 ? kDescPrefix : kDescAgg) | agg);
+}
+
+// One wavefront, all lanes, after publish(): sums the record bytes of chunks
+// 0..i-1 from their descriptors, 64 per round, back to the nearest inclusive
+// prefix, publishes chunk i's inclusive prefix and returns the exclusive one
+// (the record's offset past the table). Chunk ids follow the order of an
+// atomic ticket, and a workgroup publishes a chunk's size right after its own
+// parse, before it waits for any other, so the lowest chunk not yet published
+// never waits: every wait ends. As a guard
 // a wait of more than kLookbackPolls polls gives up; the chunk then
 // publishes and returns kDescValue ("failed"), and its successors pass it on.
 __device__ inline uint64_t lookback(uint64_t* desc, uint64_t i, uint64_t agg) {
   const uint32_t lane = lane_id();
-  if (i == 0) {
-    if (lane == 0) desc_store(desc, kDescPrefix | agg);
-    return 0;
-  }
-  if (lane == 0) desc_store(desc + i, kDescAgg | agg);
+  if (i == 0) return 0;
   uint64_t excl = 0;
   uint64_t j = i;  // chunks [0, j) not yet summed
   uint32_t polls = 0;
-  bool failed = false;
-  for (;;) {
-    // lane l reads chunk j - 1 - l; lanes past chunk 0 read an empty prefix
-    const uint64_t v = lane < j ? desc_load(desc + (j - 1 - lane)) : kDescPrefix;
-    const uint32_t st = (uint32_t)(v >> 62);
-    const uint64_t ready = ballot(st != 0);
-    const uint64_t pref = ballot(st == 2);
-    // lanes 0 .. run-1 are all published
-    const uint32_t run = ready == ~0ull ? 64u : (uint32_t)__builtin_ctzll(~ready);
-    const uint64_t pm = pref & (run == 64u ? ~0ull : ((1ull << run) - 1ull));
-    if (pm) {
-      const uint32_t pl = (uint32_t)__builtin_ctzll(pm);
-      // single-chunk sizes (lanes below pl) are far below 2^32 each
-      excl += readlane(wave_incl_scan(lane < pl ? (uint32_t)v : 0u), 63);
-      const uint64_t pv = ((uint64_t)readlane((uint32_t)(v >> 32), pl) << 32 |
-                           readlane((uint32_t)v, pl)) & kDescValue;
-      failed = pv == kDescValue;
-      excl += pv;
-      break;
+  bool failed = false, done = false, far = false;
+  while (!done) {
+    // lane l reads chunk j - 1 - l; lanes past chunk 0 read an empty prefix.
+    // Once the nearest 64 are all published, 256 a poll
+    uint64_t v[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint64_t l = lane + 64 * k;
+      v[k] = k == 0 || far ? (l < j ? desc_load(desc + (j - 1 - l)) : kDescPrefix) : 0ull;
     }
-    if (run) {
-      excl += readlane(wave_incl_scan(lane < run ? (uint32_t)v : 0u), 63);
+    bool moved = false;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+      const uint32_t st = (uint32_t)(v[k] >> 62);
+      const uint64_t ready = ballot(st != 0);
+      const uint64_t pref = ballot(st == 2);
+      // lanes 0 .. run-1 are all published
+      const uint32_t run = ready == ~0ull ? 64u : (uint32_t)__builtin_ctzll(~ready);
+      const uint64_t pm = pref & (run == 64u ? ~0ull : ((1ull << run) - 1ull));
+      const uint32_t n = pm ? (uint32_t)__builtin_ctzll(pm) : run;  // sizes to add
+      // single-chunk sizes are far below 2^32 each
+      if (n) excl += readlane(wave_incl_scan(lane < n ? (uint32_t)v[k] : 0u), 63);
+      if (pm) {
+        const uint64_t pv = ((uint64_t)readlane((uint32_t)(v[k] >> 32), n) << 32 |
+                             readlane((uint32_t)v[k], n)) & kDescValue;
+        failed = pv == kDescValue;
+        excl += pv;
+        done = true;
+        break;
+      }
       j -= run;
+      moved |= run != 0;
+      if (run != 64) break;
+    }
+    if (done) break;
+    far = moved;
+    if (moved) {
       polls = 0;
-      continue;
+    } else if (++polls > kLookbackPolls) {
+      failed = done = true;
+    } else {
+      __builtin_amdgcn_s_sleep(1);
     }
-    if (++polls > kLookbackPolls) {
-      failed = true;
-      break;
-    }
-    __builtin_amdgcn_s_sleep(4);
   }
   if (failed) excl = kDescValue;
   if (lane == 0) desc_store(desc + i, kDescPrefix | (failed ? kDescValue : excl + agg));
@@ -1291,34 +1304,36 @@ __device__ __forceinline__ void emit_group(uint32_t cnt, uint32_t desc, uint32_t
   encode_group<S>(cnt, desc, g, win, slot, flag_area, pay);
 }
 
-// One wavefront: the table entry and, if it ends within the capacity, the
-// record of chunk job.i at offset excl past the table. Flag bytes of groups
+// Threads tid < nthreads of a workgroup (whole wavefronts): the table entry and,
+// if it ends within the capacity, the record of chunk job.i at offset excl
+// past the table. Slot contents written by another wave have to be visible
+// (a barrier after them). Flag bytes of groups
 // before g0 are zero and the rest come from the slot; payload bytes before
 // group g0 (64 S per group, all literals) come from the staged chunk in LDS,
 // the rest from the slot. No byte at or past the capacity is written.
 template <int S>
 __device__ inline void write_record(const ChunkJob& job, uint64_t excl, uint32_t F, uint32_t P,
-                                    uint32_t g0, const uint8_t* stage) {
-  const uint32_t lane = lane_id();
+                                    uint32_t g0, const uint8_t* stage, uint32_t tid = lane_id(),
+                                    uint32_t nthreads = 64) {
   const uint64_t te = kHeaderBytes + 8 * job.i;
-  if (lane == 0 && te + 8 <= job.capacity)
+  if (tid == 0 && te + 8 <= job.capacity)
     *reinterpret_cast<uint64_t*>(job.out + te) = (uint64_t)F | ((uint64_t)P << 32);
   const uint64_t base = kHeaderBytes + 8 * job.N;
   if (excl == kDescValue || base + excl + F + P > job.capacity) return;
   uint8_t* rec = job.out + base + excl;
   if (g0 != kNoGroup) {
-    // the slot was written by this wavefront's lanes: complete those stores
-    // and drop any cached copy before reading it back
+    // complete the stores to the slot and drop any cached copy before
+    // reading it back
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   const uint64_t ge = 8ull * (g0 & ~1u);
   const uint32_t fz = (uint32_t)min<uint64_t>(F, ge);
-  stream::fill_zero(rec, fz, lane, 64);
-  if (F > fz) stream::copy_bytes(rec + fz, job.slot + fz, F - fz, lane, 64);
+  stream::fill_zero(rec, fz, tid, nthreads);
+  if (F > fz) stream::copy_bytes(rec + fz, job.slot + fz, F - fz, tid, nthreads);
   const uint32_t pz = (uint32_t)min<uint64_t>(P, 64ull * S * g0);
-  stream::copy_bytes(rec + F, stage, pz, lane, 64);
-  if (P > pz) stream::copy_bytes(rec + F + pz, job.slot + job.flag_area + pz, P - pz, lane, 64);
+  stream::copy_bytes(rec + F, stage, pz, tid, nthreads);
+  if (P > pz) stream::copy_bytes(rec + F + pz, job.slot + job.flag_area + pz, P - pz, tid, nthreads);
 }
 
 // Where a chunk's record goes: its F flag bytes and its payload (adjacent in
@@ -1340,6 +1355,7 @@ __device__ __forceinline__ RecordPlace place_record(const ChunkJob& job, uint32_
   RecordPlace r;
   if constexpr (kSinglePass) {
     if (threadIdx.x < 64) {
+      publish(job.desc, job.i, (uint64_t)F + P);
       const uint64_t excl = lookback(job.desc, job.i, (uint64_t)F + P);
       if (job.i + 1 == job.N) finish_stream(job, excl, (uint64_t)F + P);
       const uint64_t te = kHeaderBytes + 8 * job.i;
@@ -1452,6 +1468,89 @@ __device__ bool build_list(const uint8_t* stage, const uint32_t* hits, uint32_t 
   return ok;
 }
 
+// What wave 0's parse found: tokens, payload bytes, and the first group of 64
+// tokens with a pointer (kNoGroup if there is none).
+struct Parsed {
+  uint32_t ntok, pay, g0;
+};
+
+// The greedy parse and encoding of a staged chunk, one wavefront: candidates
+// from the hit bitmap (or, with `listed`, from the candidate list with its
+// search results; with `dense`, every position). Two-pass path: the whole
+// record goes to the slot; single-pass path: the groups from g0 on.
+template <int S, int WC, bool kSinglePass>
+__device__ __forceinline__ Parsed parse_chunk(const ChunkJob& job, const uint8_t* stage,
+                                              const uint32_t* hits, uint32_t nhw, bool sampled,
+                                              bool dense, bool listed, const uint32_t* list,
+                                              const uint64_t (&wmask)[WC], uint32_t nwaves) {
+  using T = typename SymType<S>::T;
+  const T* win = reinterpret_cast<const T*>(stage);
+  const uint32_t lane = lane_id();
+  const uint32_t c = job.c;
+  uint8_t* slot = job.slot;
+  uint32_t ntok = 0, pay = 0, desc = 0, g0 = kNoGroup;
+  uint32_t p = 0;
+  if constexpr (kStreamSearch<S>) {
+    if (dense && job.MIN <= 2) {
+      const uint32_t rest = parse_dense<S, WC>(stage, 0, c, c, job.W, job.MIN, wmask, lane,
+                                               desc, [&](uint32_t d64) {
+        emit_group<S, kSinglePass>(64, d64, ntok >> 6, win, slot, job.flag_area, pay, g0);
+        ntok += 64;
+      });
+      ntok += rest;
+      p = c;
+    }
+  }
+  CandCursor cc;
+  ListCursor lc;
+  if (listed) lc.init(list, nwaves);
+  else cc.init(hits, nhw, sampled);
+  StreamMatchFor<S, WC> sm;
+  sm.init(stage, job.W, lane);
+  while (p < c) {
+    uint32_t lkey = 0;
+    const uint32_t h = listed ? lc.next(p, c, lkey) : cc.next(p, c, hits, nhw, sampled);
+    // literals for [p, h); on the single-pass path, whole all-literal groups
+    // before the first pointer are only counted
+    if constexpr (kSinglePass) {
+      if (g0 == kNoGroup && (ntok & 63u) == 0 && h - p >= 64) {
+        const uint32_t k = (h - p) / 64;
+        ntok += 64 * k;
+        p += 64 * k;
+        pay += 64 * S * k;
+      }
+    }
+    while (p < h) {
+      const uint32_t sl = ntok & 63u;
+      const uint32_t take = min(h - p, 64u - sl);
+      if (lane >= sl && lane < sl + take) desc = (p + lane - sl) << 1;
+      ntok += take;
+      p += take;
+      if ((ntok & 63u) == 0)
+        emit_group<S, kSinglePass>(64, desc, (ntok >> 6) - 1, win, slot, job.flag_area, pay, g0);
+    }
+    if (h >= c) break;
+
+    const uint32_t key =
+        listed ? lkey : find_token<S, WC>(sm, win, h, c, job.W, job.MIN, wmask, lane);
+    uint32_t val;
+    if (key) {
+      val = 1u | ((key >> 9) << 1) | ((key & 0xFFu) << 9);
+      p = h + (key >> 9);
+    } else {
+      val = h << 1;
+      p = h + 1;
+    }
+    if (lane == (ntok & 63u)) desc = val;
+    ++ntok;
+    if ((ntok & 63u) == 0)
+      emit_group<S, kSinglePass>(64, desc, (ntok >> 6) - 1, win, slot, job.flag_area, pay, g0);
+  }
+  if (ntok & 63u)
+    emit_group<S, kSinglePass>(ntok & 63u, desc, ntok >> 6, win, slot, job.flag_area, pay, g0);
+  return {ntok, pay, g0};
+}
+
 // Encodes one chunk. Every wave of the workgroup stages the chunk and builds
 // the hit bitmap; waves other than 0 return after that, wave 0 parses and
 // encodes.
@@ -1515,7 +1614,6 @@ __device__ void encode_chunk(const ChunkJob& job, uint8_t* lds) {
     build_hits<S, WC>(stage, b0, nblocks, nwaves, job.W, c, sampled, hits);
   }
   __syncthreads();
-  const T* win = reinterpret_cast<const T*>(stage);
   uint64_t wmask[WC];
 #pragma unroll
   for (int col = 0; col < WC; ++col) wmask[col] = ballot(64u * col + lane + 1u <= job.W);
@@ -1529,73 +1627,14 @@ __device__ void encode_chunk(const ChunkJob& job, uint8_t* lds) {
   if (wave != 0) return;
 
   // ---- parse + encode: wave 0
-
-  uint8_t* slot = job.slot;
-  uint32_t ntok = 0, pay = 0, desc = 0, g0 = kNoGroup;
-  uint32_t p = 0;
-  if constexpr (kStreamSearch<S>) {
-    if (dense && job.MIN <= 2) {
-      const uint32_t rest = parse_dense<S, WC>(stage, 0, c, c, job.W, job.MIN, wmask, lane,
-                                               desc, [&](uint32_t d64) {
-        emit_group<S, kSinglePass>(64, d64, ntok >> 6, win, slot, job.flag_area, pay, g0);
-        ntok += 64;
-      });
-      ntok += rest;
-      p = c;
-    }
-  }
-  CandCursor cc;
-  ListCursor lc;
-  if (listed) lc.init(list, nwaves);
-  else cc.init(hits, nhw, sampled);
-  StreamMatchFor<S, WC> sm;
-  sm.init(stage, job.W, lane);
-  while (p < c) {
-    uint32_t lkey = 0;
-    const uint32_t h = listed ? lc.next(p, c, lkey) : cc.next(p, c, hits, nhw, sampled);
-    // literals for [p, h); on the single-pass path, whole all-literal groups
-    // before the first pointer are only counted
-    if constexpr (kSinglePass) {
-      if (g0 == kNoGroup && (ntok & 63u) == 0 && h - p >= 64) {
-        const uint32_t k = (h - p) / 64;
-        ntok += 64 * k;
-        p += 64 * k;
-        pay += 64 * S * k;
-      }
-    }
-    while (p < h) {
-      const uint32_t sl = ntok & 63u;
-      const uint32_t take = min(h - p, 64u - sl);
-      if (lane >= sl && lane < sl + take) desc = (p + lane - sl) << 1;
-      ntok += take;
-      p += take;
-      if ((ntok & 63u) == 0)
-        emit_group<S, kSinglePass>(64, desc, (ntok >> 6) - 1, win, slot, job.flag_area, pay, g0);
-    }
-    if (h >= c) break;
-
-    const uint32_t key =
-        listed ? lkey : find_token<S, WC>(sm, win, h, c, job.W, job.MIN, wmask, lane);
-    uint32_t val;
-    if (key) {
-      val = 1u | ((key >> 9) << 1) | ((key & 0xFFu) << 9);
-      p = h + (key >> 9);
-    } else {
-      val = h << 1;
-      p = h + 1;
-    }
-    if (lane == (ntok & 63u)) desc = val;
-    ++ntok;
-    if ((ntok & 63u) == 0)
-      emit_group<S, kSinglePass>(64, desc, (ntok >> 6) - 1, win, slot, job.flag_area, pay, g0);
-  }
-  if (ntok & 63u)
-    emit_group<S, kSinglePass>(ntok & 63u, desc, ntok >> 6, win, slot, job.flag_area, pay, g0);
-  const uint32_t F = (ntok + 7) / 8;
+  const Parsed r = parse_chunk<S, WC, kSinglePass>(job, stage, hits, nhw, sampled, dense, listed,
+                                                   list, wmask, nwaves);
+  const uint32_t F = (r.ntok + 7) / 8, pay = r.pay;
   if constexpr (kSinglePass) {
+    publish(job.desc, job.i, (uint64_t)F + pay);
     const uint64_t excl = lookback(job.desc, job.i, (uint64_t)F + pay);
     if (job.i + 1 == job.N) finish_stream(job, excl, (uint64_t)F + pay);
-    write_record<S>(job, excl, F, pay, g0, stage);
+    write_record<S>(job, excl, F, pay, r.g0, stage);
   } else {
     if (lane == 0) {
       job.sizes[0] = F;
@@ -2047,6 +2086,7 @@ __device__ void encode_chunk_scan(const ChunkJob& job, uint8_t* lds) {
   }
   if (ntok & 63u) emit_group<S, true>(ntok & 63u, desc, ntok >> 6, win, slot, job.flag_area, pay, g0);
   const uint32_t F = (ntok + 7) / 8;
+  publish(job.desc, job.i, (uint64_t)F + pay);
   const uint64_t excl = lookback(job.desc, job.i, (uint64_t)F + pay);
   if (job.i + 1 == job.N) finish_stream(job, excl, (uint64_t)F + pay);
   write_record<S>(job, excl, F, pay, g0, stage);

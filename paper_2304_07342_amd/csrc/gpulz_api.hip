@@ -230,9 +230,16 @@ gpulz_status gpulz_compress_policy(const void* d_in, uint64_t nbytes, uint32_t S
     std::lock_guard<std::mutex> lk(g_defaults_mu);
     waves = g_defaults[width_index(S)].waves_per_chunk;
   }
-  int pi = prof_begin(1, stream);
   clear_stale_hip_error();
-  hipError_t err = launch_fused_prep(a, stream);
+  hipError_t err;
+  if (N && takes_wide(C, S, MIN, policy)) {
+    const int pw = prof_begin(0, stream);
+    if ((err = launch_wide(a, stream)) != hipSuccess) return hip_failed(err, "compress launch");
+    prof_end(pw, stream);
+    return GPULZ_OK;
+  }
+  int pi = prof_begin(1, stream);
+  err = launch_fused_prep(a, stream);
   if (err != hipSuccess) return hip_failed(err, "compress prepare launch");
   prof_end(pi, stream);
   pi = prof_begin(0, stream);

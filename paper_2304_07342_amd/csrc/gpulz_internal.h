@@ -96,6 +96,12 @@ hipError_t launch_fused_prep(const FusedArgs& a, hipStream_t s);
 // kMaxChunksPerLaunch) with ticket a.launch, for match policy a.policy.
 hipError_t launch_fused_encode(const FusedArgs& a, uint32_t waves, hipStream_t s);
 
+// 4- and 8-byte symbols (MIN >= 2, match policy 0, chunks the sizing kernel
+// takes): the whole compression of a non-empty input with no look-back, in a
+// sizing, a scan and a writing launch; uses the descriptor area and the slots,
+// which need no preparation.
+bool takes_wide(uint32_t C, uint32_t S, uint32_t MIN, uint32_t policy);
+hipError_t launch_wide(const FusedArgs& a, hipStream_t s);
 
 size_t encode_lds_bytes(uint32_t C, uint32_t S, uint32_t W, uint32_t waves);
 size_t encode_scan_lds_bytes(uint32_t C, uint32_t S);

@@ -20,6 +20,7 @@
 // table, then a persistent decoder over all chunks.
 #include "decode_device.h"
 #include "bucket_device.h"
+#include "wide_device.h"
 #include "stream_device.h"
 
 namespace gpulz {
@@ -137,8 +138,12 @@ __global__ __launch_bounds__(kPlanThreads) void batch_enc_plan_kernel(BatchEncAr
   }
 }
 
-// kBucket: the bucket encoder with 256 threads.
-template <int S, int WC, bool kBucket>
+// Which encoder a width's persistent kernel runs: the general one, the bucket
+// encoder (1- and 2-byte symbols) or the sizing by repeated pairs (4- and 8-byte
+// symbols; chunks of at most 16 or 32 KiB), the last three with 256 threads.
+enum class BatchEncoder { kGeneral, kBucket, kWide16, kWide32 };
+
+template <int S, int WC, BatchEncoder kE>
 __device__ __forceinline__ void encode_item(const BatchEncArgs& a, uint64_t b, const BatchEncBuf& e,
                                             uint64_t i, uint8_t* lds) {
   const uint64_t cs = i * e.C;
@@ -152,15 +157,25 @@ __device__ __forceinline__ void encode_item(const BatchEncArgs& a, uint64_t b, c
   job.slot = a.slots + e.slot_base + i * e.slot_bytes;
   job.flag_area = e.flag_area;
   job.sizes = a.sizes + 2 * (e.chunk_base + i);
-  if constexpr (kBucket) enc::bucket::encode_chunk<S, WC, 256, false>(job, lds);
-  else enc::encode_chunk<S, WC>(job, lds);
+  if constexpr (kE == BatchEncoder::kBucket) {
+    enc::bucket::encode_chunk<S, WC, 256, false>(job, lds);
+  } else if constexpr (kE == BatchEncoder::kGeneral) {
+    enc::encode_chunk<S, WC>(job, lds);
+  } else {
+    constexpr uint32_t V = enc::wide::kMaxVectors / (kE == BatchEncoder::kWide16 ? 2 : 1);
+    const enc::wide::Sized z = enc::wide::size_chunk<S, WC, V>(job, lds);
+    if (threadIdx.x == 0) {
+      job.sizes[0] = z.F;
+      job.sizes[1] = z.P;
+    }
+  }
 }
 
 // Persistent encoder for the chunks of symbol width S (width index WI); the
 // window spans WC columns of 64 offsets (one window per width in a batch).
 // At least 6 waves per SIMD: the 1-byte encoder then fits in 80 VGPRs (82
 // otherwise, 5 waves) without spilling; the other widths need fewer.
-template <int S, uint32_t WI, int WC, bool kBucket>
+template <int S, uint32_t WI, int WC, BatchEncoder kE>
 __global__ __launch_bounds__(64 * enc::kEncodeWaves) __attribute__((amdgpu_waves_per_eu(6)))
 void batch_encode_kernel(BatchEncArgs a) {
   extern __shared__ __align__(16) uint8_t lds[];
@@ -175,7 +190,7 @@ void batch_encode_kernel(BatchEncArgs a) {
     if (g >= T) break;
     const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].width_base[WI]; });
     const BatchEncBuf& e = a.bufs[b];
-    encode_item<S, WC, kBucket>(a, b, e, g - e.width_base[WI], lds);
+    encode_item<S, WC, kE>(a, b, e, g - e.width_base[WI], lds);
     __syncthreads();
   }
 }
@@ -217,15 +232,15 @@ __global__ __launch_bounds__(256) void batch_scatter_kernel(BatchEncArgs a) {
     const uint64_t i = g - e.chunk_base;
     const uint32_t F = a.sizes[2 * g], P = a.sizes[2 * g + 1];
     uint8_t* out = static_cast<uint8_t*>(a.out_ptrs[b]);
-    const uint32_t tid = threadIdx.x;
-    if (tid < 8) {
-      const uint32_t v = tid < 4 ? F : P;
-      out[kHeaderBytes + 8 * i + tid] = (uint8_t)(v >> (8 * (tid & 3u)));
-    }
-    uint8_t* rec = out + kHeaderBytes + 8 * e.N + a.offs[g];
-    const uint8_t* slot = a.slots + e.slot_base + i * e.slot_bytes;
-    stream::copy_bytes(rec, slot, F, tid, blockDim.x);
-    stream::copy_bytes(rec + F, slot + e.flag_area, P, tid, blockDim.x);
+    // chunks of 4- and 8-byte symbols without a pointer (their payload is as long
+    // as the chunk: a pointer takes 2 bytes for at least one symbol) are copied
+    // from the input; the sizing by repeated pairs leaves their slots unwritten
+    const uint32_t c = (uint32_t)min<uint64_t>(e.C, e.n / e.S - i * e.C);
+    const enc::wide::Sized z = {F, P, e.S <= 2 || P != c * e.S};
+    const uint8_t* in = static_cast<const uint8_t*>(a.in_ptrs[b]);
+    enc::wide::put_record(in + i * e.C * e.S, in + e.n, a.slots + e.slot_base + i * e.slot_bytes,
+                          e.flag_area, z, out + kHeaderBytes + 8 * i,
+                          out + kHeaderBytes + 8 * e.N + a.offs[g], threadIdx.x, blockDim.x);
   }
 }
 
@@ -331,7 +346,7 @@ constexpr uint32_t kWaveThreads = 1024;
 __global__ __launch_bounds__(kWaveThreads, 8) void batch_decode_wave_kernel(BatchDecArgs a) {
   __shared__ __align__(16) uint8_t lds[kWaveThreads / 64 * dec::kWaveLds];
   if (!narrow_by_waves(a)) return;
-  const uint32_t wave = dec::uniform(threadIdx.x >> 6);
+  const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint64_t T = a.ctrl->T_all, waves = (uint64_t)gridDim.x * (kWaveThreads / 64);
   for (uint64_t g = blockIdx.x + (uint64_t)wave * gridDim.x; g < T; g += waves) {
     const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].chunk_base; });
@@ -359,14 +374,14 @@ int device_cus() {
 
 }  // namespace
 
-template <int S, uint32_t WI, int WC, bool kBucket>
+template <int S, uint32_t WI, int WC, BatchEncoder kE>
 hipError_t launch_persistent(const BatchEncArgs& a, uint32_t threads, size_t lds, hipStream_t s) {
   int per_cu = 0;
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, batch_encode_kernel<S, WI, WC, kBucket>, threads, lds);
+      &per_cu, batch_encode_kernel<S, WI, WC, kE>, threads, lds);
   if (err != hipSuccess) return err;
   if (per_cu < 1) per_cu = 1;
-  hipLaunchKernelGGL((batch_encode_kernel<S, WI, WC, kBucket>), dim3(device_cus() * per_cu),
+  hipLaunchKernelGGL((batch_encode_kernel<S, WI, WC, kE>), dim3(device_cus() * per_cu),
                      dim3(threads), lds, s, a);
   return hipGetLastError();
 }
@@ -378,10 +393,18 @@ hipError_t launch_width_wc(const BatchEncArgs& a, hipStream_t s) {
     constexpr int WF = enc::bucket::kFallbackWC<S, WC>;
     const size_t lds = enc::bucket::chunk_lds<S, WF>(C, a.wp.W[WI], 256);
     if (enc::bucket::takes(C, a.wp.MIN[WI], lds, false))
-      return launch_persistent<S, WI, WF, true>(a, 256, lds, s);
+      return launch_persistent<S, WI, WF, BatchEncoder::kBucket>(a, 256, lds, s);
+  }
+  if constexpr (S >= 4) {
+    if (takes_wide(C, S, a.wp.MIN[WI], 0)) {
+      const size_t lds = enc::wide::lds_bytes(C, S, WC);
+      if (C * S <= enc::wide::kMaxBytes / 2)
+        return launch_persistent<S, WI, WC, BatchEncoder::kWide16>(a, 256, lds, s);
+      return launch_persistent<S, WI, WC, BatchEncoder::kWide32>(a, 256, lds, s);
+    }
   }
   const uint32_t waves = a.wp.waves[WI];
-  return launch_persistent<S, WI, WC, false>(a, 64 * waves,
+  return launch_persistent<S, WI, WC, BatchEncoder::kGeneral>(a, 64 * waves,
                                              encode_lds_bytes(C, S, a.wp.W[WI], waves), s);
 }
 

@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kWaveThreads, 8) void decode_wave_kernel(DecodeArgs
   const DecodeParams p = *a.params;
   if (p.status != kOk || !by_waves(p)) return;
   if (blockIdx.x == 0 && threadIdx.x < p.r) a.out[p.m * p.S + threadIdx.x] = a.in[48 + threadIdx.x];
-  const uint32_t wave = dec::uniform(threadIdx.x >> 6);
+  const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint64_t waves = (uint64_t)gridDim.x * (kWaveThreads / 64);
   for (uint64_t i = blockIdx.x + (uint64_t)wave * gridDim.x; i < p.N; i += waves) {
     const bool ok = dec::decode_stream_chunk_wave(a.in, p, a.group_off, i, a.out,

@@ -5,6 +5,7 @@
 // and record straight into the stream. Match policy 0 (exact longest match)
 // and 1 (the paper's single window pass).
 #include "bucket_device.h"
+#include "wide_device.h"
 
 namespace gpulz {
 namespace {
@@ -37,15 +38,8 @@ __global__ __launch_bounds__(256) void prep_kernel(FusedArgs a) {
   }
 }
 
-// The chunk this workgroup encodes: the next ticket of this launch (so chunk
-// ids follow the order in which workgroups start, which the look-back needs),
-// with its stream context.
-__device__ __forceinline__ enc::ChunkJob take_chunk(const FusedArgs& a, uint32_t S,
-                                                    uint64_t* shared_item) {
-  if (threadIdx.x == 0)
-    *shared_item = a.chunk0 + atomicAdd((unsigned long long*)&a.tickets[a.launch], 1ull);
-  __syncthreads();
-  const uint64_t i = *shared_item;
+// Chunk i with its stream context.
+__device__ __forceinline__ enc::ChunkJob chunk_job(const FusedArgs& a, uint32_t S, uint64_t i) {
   const uint64_t cs = i * a.C;
   enc::ChunkJob job;
   job.src = a.in + cs * S;
@@ -69,6 +63,20 @@ __device__ __forceinline__ enc::ChunkJob take_chunk(const FusedArgs& a, uint32_t
   job.out_bytes = a.out_bytes;
   job.status = a.status;
   return job;
+}
+
+// The next ticket of this launch: chunk ids follow the order in which
+// workgroups ask for them, which the look-back needs.
+__device__ __forceinline__ uint64_t next_ticket(const FusedArgs& a) {
+  return a.chunk0 + atomicAdd((unsigned long long*)&a.tickets[a.launch], 1ull);
+}
+
+// The chunk this workgroup encodes.
+__device__ __forceinline__ enc::ChunkJob take_chunk(const FusedArgs& a, uint32_t S,
+                                                    uint64_t* shared_item) {
+  if (threadIdx.x == 0) *shared_item = next_ticket(a);
+  __syncthreads();
+  return chunk_job(a, S, *shared_item);
 }
 
 template <int S, int WC>
@@ -99,6 +107,142 @@ void encode_bucket_kernel(FusedArgs a) {
   __shared__ uint64_t item;
   const enc::ChunkJob job = take_chunk(a, S, &item);
   enc::bucket::encode_chunk<S, WC, NT, true>(job, lds);
+}
+
+// ---- 4- and 8-byte symbols with MIN >= 2: sizes, scan, records -----------------
+//
+// With the look-back a chunk holds its LDS until every chunk before it is
+// sized, which held these encoders to about 30 chunks a microsecond, whatever
+// their work (a chunk of noisy data: 9 us of work, 29 us of waiting). Here the
+// sizes come first, in any order, and the records are written by a kernel of
+// their own: a chunk without pointers is copied from the input, which is read a
+// second time (256 MiB float32 field: 520 us with the look-back).
+//
+// The workspace's descriptor area holds a word per chunk (payload bytes, flag
+// bytes << 16, pointers << 31) and the record offset of every 64th chunk.
+struct WideView {
+  uint32_t* size;
+  uint64_t* group;
+};
+__device__ __forceinline__ WideView wide_view(const FusedArgs& a) {
+  WideView v;
+  v.size = reinterpret_cast<uint32_t*>(a.desc);
+  v.group = a.desc + (a.N + 1) / 2;
+  return v;
+}
+constexpr uint32_t kWideGroup = 64;
+// Launches of at most this many chunks need no scan launch.
+constexpr uint64_t kWideSumChunks = 1024;
+__device__ __forceinline__ uint32_t wide_bytes(uint32_t size) {
+  return (size & 0xFFFFu) + (size >> 16 & 0x7FFFu);
+}
+
+
+template <int S, int WC, uint32_t kVectors>
+__global__ __launch_bounds__(enc::wide::kThreads) void wide_size_kernel(FusedArgs a) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  const uint64_t i = a.chunk0 + blockIdx.x;
+  const enc::wide::Sized z = enc::wide::size_chunk<S, WC, kVectors>(chunk_job(a, S, i), lds);
+  if (threadIdx.x == 0) wide_view(a).size[i] = z.P | z.F << 16 | (z.pointers ? 1u << 31 : 0u);
+}
+
+// One workgroup: record offsets of the groups, the header, size and status.
+constexpr uint32_t kScanThreads = 1024;
+__global__ __launch_bounds__(kScanThreads) void wide_scan_kernel(FusedArgs a) {
+  constexpr uint32_t kPer = 16;  // chunks per thread: four threads share a group
+  __shared__ uint32_t wsum[kScanThreads / 64];
+  const WideView w = wide_view(a);
+  const uint32_t tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
+  uint64_t carry = 0;
+  for (uint64_t base = 0; base < a.N; base += kScanThreads * kPer) {
+    const uint64_t i0 = base + (uint64_t)tid * kPer;
+    uint32_t x[kPer], v = 0;  // a tile's record bytes stay below 2^31
+    if (i0 + kPer <= a.N) {
+#pragma unroll
+      for (uint32_t k = 0; k < kPer; k += 4)
+        *reinterpret_cast<uint4*>(x + k) = *reinterpret_cast<const uint4*>(w.size + i0 + k);
+    } else {
+#pragma unroll
+      for (uint32_t k = 0; k < kPer; ++k) x[k] = i0 + k < a.N ? w.size[i0 + k] : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) v += wide_bytes(x[k]);
+    const uint32_t incl = wave_incl_scan(v);
+    if (lane == 63) wsum[wid] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+    for (uint32_t k = 0; k < kScanThreads / 64; ++k) {
+      const uint32_t y = wsum[k];
+      before += k < wid ? y : 0u;
+      total += y;
+    }
+    if (tid % (kWideGroup / kPer) == 0 && i0 < a.N) w.group[i0 / kWideGroup] = carry + before + incl - v;
+    carry += total;
+    __syncthreads();
+  }
+  const uint64_t total = kHeaderBytes + 8 * a.N + carry;
+  const bool fits = total <= a.capacity;
+  if (tid == 0) {
+    *a.out_bytes = total;
+    *a.status = fits ? kOk : kOutOfSpace;
+  }
+  if (fits && tid < kHeaderBytes)
+    a.out[tid] = stream::header_byte(tid, a.nbytes, a.S, a.C, a.W, a.MIN, a.policy, a.N, total,
+                                     a.in + a.nbytes / a.S * a.S);
+}
+
+// kSum: no scan launch came before; every workgroup adds up all sizes itself, and
+// the first writes the header, size and status.
+template <int S, bool kSum>
+__global__ __launch_bounds__(enc::wide::kThreads) void wide_write_kernel(FusedArgs a) {
+  const WideView w = wide_view(a);
+  const uint64_t i = a.chunk0 + blockIdx.x;
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  uint64_t off;
+  uint32_t own;
+  if constexpr (kSum) {
+    __shared__ uint32_t sums[2 * enc::wide::kThreads / 64];
+    uint32_t before = 0, all = 0;  // kWideSumChunks records: below 2^31
+    for (uint32_t k = tid; k < a.N; k += enc::wide::kThreads) {
+      const uint32_t x = wide_bytes(w.size[k]);
+      before += k < i ? x : 0u;
+      all += x;
+    }
+    before = readlane(wave_incl_scan(before), 63);
+    all = readlane(wave_incl_scan(all), 63);
+    if (lane == 0) {
+      sums[2 * (tid >> 6)] = before;
+      sums[2 * (tid >> 6) + 1] = all;
+    }
+    __syncthreads();
+    off = 0;
+    uint64_t total = kHeaderBytes + 8 * a.N;
+#pragma unroll
+    for (uint32_t k = 0; k < enc::wide::kThreads / 64; ++k) {
+      off += sums[2 * k];
+      total += sums[2 * k + 1];
+    }
+    const bool fits = total <= a.capacity;
+    if (i == 0 && tid == 0) {
+      *a.out_bytes = total;
+      *a.status = fits ? kOk : kOutOfSpace;
+    }
+    if (!fits) return;  // nothing is written
+    if (i == 0 && tid < kHeaderBytes)
+      a.out[tid] = stream::header_byte(tid, a.nbytes, a.S, a.C, a.W, a.MIN, a.policy, a.N, total,
+                                       a.in + a.nbytes / a.S * a.S);
+    own = w.size[i];
+  } else {
+    if (*a.status != kOk) return;  // the stream does not fit: nothing is written
+    const uint64_t g = i / kWideGroup;
+    const uint32_t x = g * kWideGroup + lane <= i ? w.size[g * kWideGroup + lane] : 0u;
+    own = readlane(x, (uint32_t)(i % kWideGroup));
+    off = w.group[g] + readlane(wave_incl_scan(wide_bytes(x)), 63) - wide_bytes(own);
+  }
+  const enc::wide::Sized z = {own >> 16 & 0x7FFFu, own & 0xFFFFu, own >> 31 != 0};
+  enc::wide::put_record(a.in + i * a.C * S, a.in + a.nbytes, a.slots + i * a.slot_bytes,
+                        a.flag_area, z, a.out + kHeaderBytes + 8 * i,
+                        a.out + kHeaderBytes + 8 * a.N + off, tid, enc::wide::kThreads);
 }
 
 // Policy-1 chunk encoder kernel: one workgroup per chunk.
@@ -167,6 +311,58 @@ hipError_t launch_fused_prep(const FusedArgs& a, hipStream_t s) {
   const uint64_t blocks = want < 1024 ? want : 1024;
   hipLaunchKernelGGL(prep_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, a);
   return hipGetLastError();
+}
+
+bool takes_wide(uint32_t C, uint32_t S, uint32_t MIN, uint32_t policy) {
+  return policy == 0 && enc::wide::takes(C, S, MIN) &&
+         enc::wide::lds_bytes(C, S, 4) <= kMaxGroupLdsBytes;
+}
+
+namespace {
+template <int S, int WC>
+void launch_size(const FusedArgs& a, hipStream_t s) {
+  const dim3 grid((uint32_t)a.nchunks), block(enc::wide::kThreads);
+  const size_t lds = enc::wide::lds_bytes(a.C, S, WC);
+  if (a.C * S <= enc::wide::kMaxBytes / 2)
+    hipLaunchKernelGGL((wide_size_kernel<S, WC, enc::wide::kMaxVectors / 2>), grid, block, lds, s, a);
+  else
+    hipLaunchKernelGGL((wide_size_kernel<S, WC, enc::wide::kMaxVectors>), grid, block, lds, s, a);
+}
+template <int S>
+hipError_t launch_wide_s(FusedArgs a, hipStream_t s) {
+  auto each = [&](auto launch) {
+    for (uint64_t c0 = 0; c0 < a.N; c0 += kMaxChunksPerLaunch) {
+      a.chunk0 = c0;
+      a.nchunks = a.N - c0 < kMaxChunksPerLaunch ? a.N - c0 : kMaxChunksPerLaunch;
+      launch();
+    }
+  };
+  each([&] {
+    switch ((a.W + 63) / 64) {
+      case 1: launch_size<S, 1>(a, s); break;
+      case 2: launch_size<S, 2>(a, s); break;
+      case 3: launch_size<S, 3>(a, s); break;
+      default: launch_size<S, 4>(a, s); break;
+    }
+  });
+  if (a.N <= kWideSumChunks) {
+    each([&] {
+      hipLaunchKernelGGL((wide_write_kernel<S, true>), dim3((uint32_t)a.nchunks),
+                         dim3(enc::wide::kThreads), 0, s, a);
+    });
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(wide_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, a);
+  each([&] {
+    hipLaunchKernelGGL((wide_write_kernel<S, false>), dim3((uint32_t)a.nchunks),
+                       dim3(enc::wide::kThreads), 0, s, a);
+  });
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_wide(const FusedArgs& a, hipStream_t s) {
+  return a.S == 4 ? launch_wide_s<4>(a, s) : launch_wide_s<8>(a, s);
 }
 
 hipError_t launch_fused_encode(const FusedArgs& a, uint32_t waves, hipStream_t s) {

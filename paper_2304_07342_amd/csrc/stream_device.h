@@ -80,6 +80,56 @@ __device__ inline void copy_bytes(uint8_t* dst, const uint8_t* src, uint32_t len
   for (uint32_t b = head + 16 * nw + tid; b < len; b += nthreads) dst[b] = src[b];
 }
 
+// 16 bytes starting sh bytes (0..3) past the dword at q (global memory),
+// funnel-shifted from dword reads that never reach in_end.
+__device__ __forceinline__ uint4 load_group(const uint32_t* q, uint32_t sh, const uint8_t* in_end) {
+  uint32_t d[5];
+  __builtin_memcpy(d, __builtin_assume_aligned(q, 4), 16);
+  d[4] = 0;
+  if (sh) {
+    // the fifth dword holds the group's last sh bytes; at the end of the
+    // stream it is read byte by byte
+    const uint8_t* q4 = reinterpret_cast<const uint8_t*>(q + 4);
+    if (q4 + 4 <= in_end) {
+      d[4] = q[4];
+    } else {
+      for (uint32_t b = 0; b < sh; ++b) d[4] |= (uint32_t)q4[b] << (8 * b);
+    }
+  }
+  return make_uint4(__builtin_amdgcn_alignbyte(d[1], d[0], sh), __builtin_amdgcn_alignbyte(d[2], d[1], sh),
+                    __builtin_amdgcn_alignbyte(d[3], d[2], sh), __builtin_amdgcn_alignbyte(d[4], d[3], sh));
+}
+
+// Copies len bytes between any two addresses of global memory: bytes up to the
+// first 16-byte aligned destination word, aligned 16-byte words (each from
+// dword-aligned reads, funnel-shifted by the same offset), the last bytes. No
+// dword that reaches src_end is read. Four words per thread in flight.
+__device__ inline void copy_unaligned(uint8_t* dst, const uint8_t* src, uint32_t len,
+                                      const uint8_t* src_end, uint32_t tid, uint32_t nthreads) {
+  uint32_t head = (uint32_t)((16u - ((uintptr_t)dst & 15u)) & 15u);
+  if (head > len) head = len;
+  for (uint32_t b = tid; b < head; b += nthreads) dst[b] = src[b];
+  const uint32_t nw = (len - head) / 16;
+  uint4* d4 = reinterpret_cast<uint4*>(dst + head);
+  const uint8_t* s = src + head;
+  const uint32_t sh = (uint32_t)((uintptr_t)s & 3u);
+  const uint32_t* sw = reinterpret_cast<const uint32_t*>(s - sh);
+  for (uint32_t k0 = tid; k0 < nw; k0 += 4 * nthreads) {
+    uint4 g[4];
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint32_t k = k0 + j * nthreads;
+      if (k < nw) g[j] = load_group(sw + 4 * k, sh, src_end);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint32_t k = k0 + j * nthreads;
+      if (k < nw) d4[k] = g[j];
+    }
+  }
+  for (uint32_t b = head + 16 * nw + tid; b < len; b += nthreads) dst[b] = src[b];
+}
+
 // Writes len zero bytes at any destination: bytes up to the first 16-byte
 // boundary, aligned 16-byte words, then the last bytes (the edges never touch
 // a neighbour's bytes).

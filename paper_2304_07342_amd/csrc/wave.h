@@ -28,6 +28,12 @@ __device__ __forceinline__ uint32_t readlane(uint32_t v, uint32_t lane) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane);
 }
 
+// A wave-uniform value in a scalar register.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uniform(uint64_t v) {
+  return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
+}
+
 // Inclusive prefix sum across the wave, in registers (DPP): shifts by 1, 2,
 // 4 and 8 lanes within each 16-lane row (lanes shifted in from outside the
 // row read 0), then the GFX9 row broadcasts add row 0's total to row 1, row

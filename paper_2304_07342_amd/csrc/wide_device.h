@@ -1,0 +1,262 @@
+// Chunk sizing for 4- and 8-byte symbols with MIN >= 2: pointers are looked for
+// only where a pair of symbols repeats, found by hashing instead of comparing
+// every position with its window.
+#pragma once
+
+#include "encode_device.h"
+
+namespace gpulz {
+namespace enc {
+namespace wide {
+
+// A match of MIN >= 2 symbols starts at p only if the pair (sym[p], sym[p + 1])
+// also stands at an earlier position. Repeated pairs are found by hashing the
+// whole chunk: every pair sets its bit in a bitmap, and a pair that finds it set
+// sets that bit in a second one; pairs whose bit is in the second bitmap go
+// into the next round, with another hash and a smaller bitmap. Equal pairs
+// stay together in every round, chance collisions shrink (4096 pairs: about
+// 250 after the first round, 8, 0), so that a chunk of noisy data is known to be
+// all literals after three rounds, without having been staged. Other chunks are
+// staged, and their candidates searched exactly. Candidates of any distance are
+// kept (the search decides), so the window does not matter here.
+//
+// Bound by instruction issue: about 30 vector instructions and 2 LDS accesses per
+// 64 positions (W / 2 vector and as many scalar ones with the window
+// comparison).
+constexpr uint32_t kThreads = 256;
+constexpr uint32_t kMaxVectors = 8;       // 16-byte vectors a thread holds, at most
+constexpr uint32_t kMaxBytes = 16 * kMaxVectors * kThreads;  // largest chunk
+constexpr uint32_t kBits = 1u << 16;      // first round
+constexpr uint32_t kSmallBits = 1u << 13;  // later rounds
+constexpr uint32_t kListMax = 1024;       // pairs in question after a round
+constexpr uint32_t kKeep = 128;           // candidates handed to the searches
+constexpr uint32_t kShared = 16 + kKeep / 2;  // shared words, then the candidates
+constexpr uint32_t kRepetitive = ~0u;
+
+// LDS: the bitmaps (2 x 8 KiB; after the first round the lists and the small
+// bitmaps lie in the first half), overlaid by the staged chunk with its hit
+// bitmap and candidate list; then the shared words.
+__host__ __device__ constexpr uint64_t area_bytes(uint32_t C, uint32_t S, uint32_t wc) {
+  const uint64_t e = align_up(encode_lds(C, S, wc, kEncodeWaves), 16), b = 2 * kBits / 8;
+  return e > b ? e : b;
+}
+__host__ __device__ constexpr uint64_t lds_bytes(uint32_t C, uint32_t S, uint32_t wc) {
+  return area_bytes(C, S, wc) + 4 * kShared;
+}
+__host__ __device__ constexpr bool takes(uint32_t C, uint32_t S, uint32_t MIN) {
+  return S >= 4 && MIN >= 2 && (uint64_t)C * S <= kMaxBytes;
+}
+
+// 16-bit hash of the pair (a, b) for round r: 24-bit multiplies (full rate),
+// with the high bits folded in, as integers may differ in them only.
+template <int S>
+__device__ __forceinline__ uint32_t hash_pair(typename SymType<S>::T a, typename SymType<S>::T b,
+                                              uint32_t r) {
+  auto m24 = [](uint32_t x, uint32_t k) { return (x & 0xFFFFFFu) * k; };
+  const uint32_t k0 = r == 0 ? 0x9E3779u : r == 1 ? 0x165667u : 0xBF5847u;
+  const uint32_t k1 = r == 0 ? 0x85EBCBu : r == 1 ? 0xD3A265u : 0x6C8E95u;
+  uint32_t h;
+  if constexpr (S == 4) {
+    h = m24(a ^ a >> 11, k0) + m24(b ^ b >> 11, k1);
+  } else {
+    const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32);
+    const uint32_t bl = (uint32_t)b, bh = (uint32_t)(b >> 32);
+    h = m24(al ^ ah >> 11, k0) + m24(ah ^ al >> 13, 0xC2B2AFu) + m24(bl ^ bh >> 11, k1) +
+        m24(bh ^ bl >> 13, 0x27D4EBu);
+  }
+  return h >> 16;
+}
+
+// Sets bit h of `seen`, and of `twice` if it was set.
+__device__ __forceinline__ void mark(uint32_t* seen, uint32_t* twice, uint32_t h) {
+  const uint32_t b = 1u << (h & 31u);
+  if (atomicOr(&seen[h >> 5], b) & b) atomicOr(&twice[h >> 5], b);
+}
+__device__ __forceinline__ bool marked(const uint32_t* twice, uint32_t h) {
+  return twice[h >> 5] >> (h & 31u) & 1u;
+}
+
+// Candidate positions of the chunk at src (c symbols, at most kVectors 16-byte
+// vectors per thread), whole workgroup: their number, with the positions in
+// keep[], or kRepetitive if too many pairs repeat. Uniform.
+template <int S, uint32_t kVectors>
+__device__ __forceinline__ uint32_t candidates(const uint8_t* src, uint32_t c, uint8_t* area,
+                                               uint32_t* shared, uint16_t* keep) {
+  using T = typename SymType<S>::T;
+  constexpr uint32_t V = 16 / S;
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t n = c - 1;  // pairs
+  const T* sym = reinterpret_cast<const T*>(src);
+  uint32_t* seen = reinterpret_cast<uint32_t*>(area);
+  uint32_t* twice = seen + kBits / 32;
+  uint16_t* list = reinterpret_cast<uint16_t*>(area);  // two lists of kListMax
+  uint32_t* small = reinterpret_cast<uint32_t*>(list + 2 * kListMax);
+  // ---- first round: V consecutive pairs per vector, hashes kept two a word
+  T v[kVectors][V + 1];
+#pragma unroll
+  for (uint32_t k = 0; k < kVectors; ++k) {
+    const uint32_t p = V * (tid + kThreads * k);
+    if (p + V < c) {
+      __builtin_memcpy(v[k], sym + p, 16);
+      v[k][V] = sym[p + V];
+    } else {
+#pragma unroll
+      for (uint32_t e = 0; e <= V; ++e) v[k][e] = p + e < c ? sym[p + e] : T(0);
+    }
+  }
+  for (uint32_t k = tid; k < 2 * kBits / 128; k += kThreads)
+    reinterpret_cast<uint4*>(area)[k] = make_uint4(0, 0, 0, 0);
+  if (tid < 4) shared[tid] = 0;
+  __syncthreads();
+  uint32_t hs[kVectors][V / 2];
+#pragma unroll
+  for (uint32_t k = 0; k < kVectors; ++k) {
+    const uint32_t p = V * (tid + kThreads * k);
+    const bool whole = V * kThreads * (k + 1) <= n;  // uniform: every lane's pairs exist
+#pragma unroll
+    for (uint32_t e = 0; e < V; ++e) {
+      const uint32_t h = hash_pair<S>(v[k][e], v[k][e + 1], 0);
+      if (e % 2 == 0) hs[k][e / 2] = h;
+      else hs[k][e / 2] |= h << 16;
+      if (whole || p + e < n) mark(seen, twice, h);
+    }
+  }
+  __syncthreads();
+  uint32_t mine = 0;  // bit V k + e: pair e of vector k is in question
+#pragma unroll
+  for (uint32_t k = 0; k < kVectors; ++k) {
+    const uint32_t p = V * (tid + kThreads * k);
+    const bool whole = V * kThreads * (k + 1) <= n;
+#pragma unroll
+    for (uint32_t e = 0; e < V; ++e) {
+      const uint32_t h = e % 2 ? hs[k][e / 2] >> 16 : hs[k][e / 2] & 0xFFFFu;
+      const uint32_t bit = (uint32_t)marked(twice, h);
+      mine |= (whole || p + e < n ? bit : 0u) << (V * k + e);
+    }
+  }
+  {
+    const uint32_t cnt = (uint32_t)__popc(mine), incl = wave_incl_scan(cnt);
+    const uint32_t all = readlane(incl, 63);
+    uint32_t base = 0;
+    if (lane == 0 && all) base = atomicAdd(&shared[0], all);
+    uint32_t at = readlane(base, 0) + incl - cnt;
+    // (the lists lie in `seen`, which the marks above no longer touch)
+    for (uint32_t m = mine; m; m &= m - 1, ++at) {
+      const uint32_t b = (uint32_t)__builtin_ctz(m);
+      if (at < kListMax) list[at] = (uint16_t)(V * (tid + kThreads * (b / V)) + b % V);
+    }
+  }
+  for (uint32_t k = tid; k < 2 * kSmallBits / 32; k += kThreads) small[k] = 0;
+  __syncthreads();
+  uint32_t left = uniform(shared[0]);
+  if (left > kListMax) return kRepetitive;
+  // ---- later rounds: one pair of the list per thread at a time
+#pragma unroll 1
+  for (uint32_t r = 1; r <= 2 && left; ++r) {
+    uint32_t* seen2 = small;
+    uint32_t* twice2 = small + kSmallBits / 32;
+    const uint16_t* from = list + (r - 1) * kListMax;
+    uint16_t* to = r == 1 ? list + kListMax : keep;
+    const uint32_t cap = r == 1 ? kListMax : kKeep;
+    for (uint32_t k = tid; k < left; k += kThreads) {
+      const uint32_t p = from[k];
+      mark(seen2, twice2, hash_pair<S>(sym[p], sym[p + 1], r) % kSmallBits);
+    }
+    __syncthreads();
+    for (uint32_t k = tid; k < left; k += kThreads) {
+      const uint32_t p = from[k];
+      if (marked(twice2, hash_pair<S>(sym[p], sym[p + 1], r) % kSmallBits)) {
+        const uint32_t at = atomicAdd(&shared[r], 1u);
+        if (at < cap) to[at] = (uint16_t)p;
+      }
+    }
+    __syncthreads();
+    left = uniform(shared[r]);
+    if (left > cap) return kRepetitive;
+    if (r == 1 && left) {
+      for (uint32_t k = tid; k < 2 * kSmallBits / 32; k += kThreads) small[k] = 0;
+      __syncthreads();
+    }
+  }
+  return left;
+}
+
+// Sizes of a chunk's record, and whether it has pointers.
+struct Sized {
+  uint32_t F, P;
+  bool pointers;
+};
+
+// Sizes one chunk, whole workgroup of kThreads; a record with pointers is written
+// to the chunk's slot, others are their flag zeros and the chunk itself.
+template <int S, int WC, uint32_t kVectors>
+__device__ __forceinline__ Sized size_chunk(const ChunkJob& job, uint8_t* lds) {
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t c = job.c;
+  uint32_t* shared = reinterpret_cast<uint32_t*>(lds + area_bytes(job.C, S, WC));
+  uint16_t* keep = reinterpret_cast<uint16_t*>(shared + 16);
+  const Sized literals = {(c + 7) / 8, c * S, false};
+  const uint32_t ncand = candidates<S, kVectors>(job.src, c, lds, shared, keep);
+  if (ncand == 0) return literals;
+  __syncthreads();
+  uint8_t* stage = lds + pad_bytes<S, WC>();
+  uint32_t* hits = reinterpret_cast<uint32_t*>(stage + chunk_lds_bytes(job.C, S));
+  const uint32_t nhw = (uint32_t)hit_words(job.C, S);
+  uint32_t* list = hits + nhw;
+  stage_chunk<S>(job, stage);
+  for (uint32_t k = tid; k < nhw; k += kThreads) hits[k] = 0;
+  __syncthreads();
+  const bool sampled = ncand == kRepetitive;
+  if (sampled) {  // the window comparison of every second position
+    constexpr uint32_t kBlock = Geo<S>::kBlock;
+    build_hits<S, WC>(stage, wave, (c + kBlock - 1) / kBlock, kThreads / 64, job.W, c, true, hits);
+  } else if (tid < ncand) {
+    atomicOr(&hits[keep[tid] >> 5], 1u << (keep[tid] & 31u));
+  }
+  __syncthreads();
+  uint64_t wmask[WC];
+#pragma unroll
+  for (int col = 0; col < WC; ++col) wmask[col] = ballot(64u * col + lane + 1u <= job.W);
+  const bool listed = build_list<S, WC>(stage, hits, nhw, sampled, job, wmask, list, wave,
+                                        kThreads / 64);
+  if (listed) {  // no search found a match: literals only
+    const uint32_t* key = list + kEncodeWaves * kListPerWave;
+    const uint32_t* cnt = key + kEncodeWaves * kListPerWave;
+    bool any = false;
+    for (uint32_t w = 0; w < kEncodeWaves; ++w)
+      any |= lane < cnt[w] && key[w * kListPerWave + lane] != 0;
+    if (ballot(any) == 0) return literals;
+  }
+  if (wave == 0) {
+    const Parsed r = parse_chunk<S, WC, false>(job, stage, hits, nhw, sampled, false, listed, list,
+                                               wmask, kThreads / 64);
+    if (lane == 0) {
+      shared[0] = r.ntok;
+      shared[1] = r.pay;
+    }
+  }
+  __syncthreads();
+  return {(uniform(shared[0]) + 7) / 8, uniform(shared[1]), true};
+}
+
+// Writes a chunk's record, whole workgroup: the table entry, the flag bytes and
+// the payload, from the chunk itself (src) if it has no pointer, else from the
+// slot. in_end: end of the input (no dword that reaches it is read).
+__device__ __forceinline__ void put_record(const uint8_t* src, const uint8_t* in_end,
+                                           const uint8_t* slot, uint64_t flag_area, const Sized& z,
+                                           uint8_t* table, uint8_t* rec, uint32_t tid,
+                                           uint32_t nthreads) {
+  if (tid < 8) table[tid] = (uint8_t)((tid < 4 ? z.F : z.P) >> (8 * (tid & 3u)));
+  if (z.pointers) {
+    stream::copy_bytes(rec, slot, z.F, tid, nthreads);
+    stream::copy_bytes(rec + z.F, slot + flag_area, z.P, tid, nthreads);
+  } else {
+    stream::fill_zero(rec, z.F, tid, nthreads);
+    stream::copy_unaligned(rec + z.F, src, z.P, in_end, tid, nthreads);
+  }
+}
+
+}  // namespace wide
+}  // namespace enc
+}  // namespace gpulz
