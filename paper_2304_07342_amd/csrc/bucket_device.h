@@ -116,6 +116,24 @@ __device__ __forceinline__ uint32_t first_bit(uint32_t x) {
   return r;
 }
 
+// Four 1- or 2-byte symbols from symbol address p of the stage, and the leading
+// equal symbols (0..4) of two such words.
+template <int S>
+__device__ __forceinline__ typename SymType<4 * S>::T load4(const uint8_t* stage, uint32_t p) {
+  const uint32_t a = p * S;
+  return load_run<S>(reinterpret_cast<const uint32_t*>(stage + (a & ~3u)), a & 3u);
+}
+template <int S>
+__device__ __forceinline__ uint32_t equal4(typename SymType<4 * S>::T x,
+                                           typename SymType<4 * S>::T y) {
+  if constexpr (S == 1) {
+    return min(first_bit(x ^ y), 32u) >> 3;
+  } else {
+    const uint64_t e = x ^ y;
+    return min(min(first_bit((uint32_t)e), first_bit((uint32_t)(e >> 32)) | 32u), 64u) >> 4;
+  }
+}
+
 // The second largest of a >= b and x.
 __device__ __forceinline__ uint32_t second_of(uint32_t a, uint32_t b, uint32_t x) {
   uint32_t r;
@@ -302,6 +320,169 @@ __device__ __forceinline__ SearchEnd search(const uint8_t* stage, const uint8_t*
   return kSearched;
 }
 
+// ---- match policy 1 (the paper's single window pass, see encode_chunk_scan) ------
+//
+// The walk of a position p goes through the window's slots from the oldest on:
+// a slot unlike sym[p] is passed over, an equal one starts a run of L equal
+// symbols (L at most p - w, 255 and what is left of the chunk), which counts
+// if strictly longer than the best one, and the walk goes on past the slot
+// where the run stopped. So only the equal slots matter: each lane first
+// compares its symbol with 32 slots (two vector instructions a slot: compare,
+// and shift the result into a mask), then takes the mask's bits in order. The
+// step-by-step walk takes some twenty instructions a slot.
+//
+// For 1- and 2-byte symbols, where every sixth slot or so is equal, a second mask
+// tells the slots whose next symbol matches, too, and only those are taken: a
+// run of one symbol cannot win (MIN >= 2), and only passes over the slot after
+// it. Of r equal slots right before a slot, all runs of one, every second one
+// is such a start: the slot is passed over if r is odd.
+
+// m = 2 m + (a == b).
+template <int S>
+__device__ __forceinline__ void push_equal(uint32_t& m, typename SymType<S>::T a,
+                                           typename SymType<S>::T b) {
+  if constexpr (S == 8) {
+    asm("v_cmp_eq_u64 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
+        : "+v"(m) : "v"(a), "v"(b) : "vcc");
+  } else if constexpr (S == 4) {
+    asm("v_cmp_eq_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
+        : "+v"(m) : "v"(a), "v"(b) : "vcc");
+  } else {
+    asm("v_cmp_eq_u16 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
+        : "+v"(m) : "v"((uint32_t)a), "v"((uint32_t)b) : "vcc");
+  }
+}
+
+// Equality of x with the 32 symbols from symbol address w on (w may be before
+// the chunk: the pad is read), the first in bit 31.
+template <int S>
+__device__ __forceinline__ uint32_t equal32(const uint8_t* stage, int32_t w,
+                                            typename SymType<S>::T x) {
+  using T = typename SymType<S>::T;
+  uint32_t m = 0;
+  if constexpr (S >= 4) {
+    const T* y = reinterpret_cast<const T*>(stage) + w;
+#pragma unroll
+    for (uint32_t t = 0; t < 32; ++t) push_equal<S>(m, y[t], x);
+  } else {
+    const int32_t at = w * S;
+    const uint32_t* y = reinterpret_cast<const uint32_t*>(stage + (at & ~3));
+    uint32_t a = y[0];
+#pragma unroll
+    for (uint32_t t = 0; t < 8 * S; ++t) {  // a dword of 4 / S symbols at a time
+      const uint32_t b = y[t + 1];
+      const uint32_t v = __builtin_amdgcn_alignbyte(b, a, (uint32_t)at);
+      a = b;
+#pragma unroll
+      for (uint32_t e = 0; e < 4 / S; ++e) push_equal<S>(m, (T)(v >> (8 * S * e)), x);
+    }
+  }
+  return m;
+}
+
+// Policy-1 results of every position into res (all waves of NT threads).
+template <int S, int NT>
+__device__ __forceinline__ void scan_search(const uint8_t* stage, uint32_t c, uint32_t W,
+                                            uint32_t MIN, uint16_t* res, uint32_t seg_sh) {
+  using T = typename SymType<S>::T;
+  const T* sym = reinterpret_cast<const T*>(stage);
+  for (uint32_t p = threadIdx.x; p - lane_id() < c; p += NT) {
+    const bool in = p < c;
+    const T x = sym[in ? p : 0u];
+    [[maybe_unused]] typename SymType<S >= 4 ? 4 : 4 * S>::T x4{};
+    [[maybe_unused]] T x1{};
+    if constexpr (S <= 2) {
+      x4 = load4<S>(stage, in ? p : 0u);
+      x1 = (T)(x4 >> (8 * S));
+    }
+    const int32_t w0 = (int32_t)p - (int32_t)W;  // the oldest slot
+    int32_t cur = w0 < 0 ? 0 : w0;               // the next slot to look at
+    uint32_t bestL = 0, bestd = 0;
+    bool on = in;
+    for (uint32_t k = 0; k < W; k += 32) {
+      const int32_t g = w0 + (int32_t)k;  // slot of bit 31
+      const uint32_t n = min(32u, W - k);  // slots of this mask
+      const uint32_t all = equal32<S>(stage, g, x);
+      uint32_t m = all;
+      if constexpr (S <= 2) m &= equal32<S>(stage, g + 1, x1);
+      m &= (uint32_t)(~0ull << 32 >> n);  // the first n slots
+      const int32_t skip = cur - g;
+      if (skip > 0) m = skip >= 32 ? 0u : m & (~0u >> skip);
+      if (!on) m = 0;
+      // takes the run of L symbols at slot w
+      auto take = [&](int32_t w, uint32_t d, uint32_t L) {
+        if (L > bestL) {
+          bestL = L;
+          bestd = d;
+        }
+        cur = w + (int32_t)L + 1;
+        on = L < d && p + L < c;  // else the walk has reached p or the chunk's end
+        const uint32_t past = (uint32_t)(cur - g);
+        m = !on || past >= 32 ? 0u : m & (~0u >> past);
+      };
+      // equal slots right before slot t of the mask, back to `cur` at most
+      auto run_before = [&](uint32_t t) {
+        const uint32_t ones = first_bit(~(uint32_t)((uint64_t)all >> (32 - t)));
+        return min(ones, t - (uint32_t)min(max(cur - g, 0), (int32_t)t));
+      };
+      if constexpr (S >= 4) {
+        while (m) {
+          const int32_t w = g + __builtin_clz(m);
+          const uint32_t d = p - (uint32_t)w, lim = min(min(d, kMaxMatch), c - p);
+          uint32_t L = 1;
+          while (L < lim && sym[p + L] == sym[w + (int32_t)L]) ++L;
+          take(w, d, L);
+        }
+      } else {
+        // runs of four symbols and more wait until every lane has one (or is
+        // done), and are extended together
+        bool waits = false;
+        while (ballot(m != 0)) {
+          const uint32_t t = m ? (uint32_t)__builtin_clz(m) : 0u;
+          const int32_t w = g + (int32_t)t;
+          const uint32_t d = p - (uint32_t)w, lim = min(min(d, kMaxMatch), c - p);
+          if (ballot(m != 0 && !waits)) {
+            if (m != 0 && !waits) {
+              if (run_before(t) & 1u) {
+                cur = w + 1;
+                m &= ~(1u << (31 - t));
+              } else {
+                const uint32_t L = equal4<S>(x4, load4<S>(stage, (uint32_t)w));
+                if (L == 4 && lim > 4) waits = true;
+                else take(w, d, min(max(L, 1u), lim));
+              }
+            }
+          } else if (waits) {
+            uint32_t L = 4;
+            while (L < lim) {
+              const uint32_t e = equal4<S>(load4<S>(stage, p + L), load4<S>(stage, (uint32_t)w + L));
+              L += e;
+              if (e < 4) break;
+            }
+            take(w, d, min(L, lim));
+            waits = false;
+          }
+        }
+        // a run of one symbol at the mask's last slot passes over the next one
+        cur = max(cur, g + (int32_t)(n + (run_before(n) & 1u)));
+      }
+    }
+    if (in) res[res_at(p, seg_sh)] = (uint16_t)(bestL >= MIN ? bestL << 8 | (bestd & 0xFFu) : 0u);
+  }
+}
+
+// LDS of a policy-1 chunk.
+__host__ __device__ constexpr uint64_t scan_lds(uint32_t C, uint32_t S, uint32_t threads) {
+  const uint32_t sh = seg_shift(C, threads);
+  const uint64_t parse = segments(C, sh) * (8 + 4 + 4) + align_up(C, 64) / 8;
+  return pad_for(S, 4) + chunk_lds_bytes(C, S) + align_up(res_bytes(C, sh), 16) +
+         align_up(parse, 16) + 4 * kShared;
+}
+// Policy-1 chunks with table entries the parse can tell from its marks.
+__host__ constexpr bool takes_scan(uint32_t C, uint32_t S, uint32_t MIN, uint32_t threads) {
+  return MIN >= 2 && C <= kMaxSyms && scan_lds(C, S, threads) <= kMaxGroupLdsBytes;
+}
+
 // Greedy parse from LDS results: lane g of the workgroup takes segment g. All segments are parsed at once, each as if a token started
 // at its first position; then every segment is entered where the one before
 // it ends, again and again until nothing changes. Two parses that meet at a
@@ -396,9 +577,10 @@ template <int S, int WC> struct SegmentParse {
   }
 };
 
-// Encodes one chunk (the same stream as encode_chunk). All waves of the
-// workgroup of NT threads take part throughout.
-template <int S, int WC, int NT, bool kSinglePass>
+// Encodes one chunk (the same stream as enc::encode_chunk, or with kScan
+// enc::encode_chunk_scan). All waves of the workgroup of NT threads take part
+// throughout.
+template <int S, int WC, int NT, bool kSinglePass, bool kScan = false>
 __device__ __forceinline__ void encode_chunk(const ChunkJob& job, uint8_t* lds) {
   using Sym = typename SymType<S>::T;
   constexpr uint32_t kWaves = NT / 64;
@@ -407,29 +589,37 @@ __device__ __forceinline__ void encode_chunk(const ChunkJob& job, uint8_t* lds) 
   const uint32_t c = __builtin_amdgcn_readfirstlane(job.c);
   uint8_t* stage = lds + pad_bytes<S, WC>();
   uint8_t* low = stage + chunk_lds_bytes(job.C, S);
-  uint16_t* res = reinterpret_cast<uint16_t*>(low + low_bytes(job.C, S));
+  uint16_t* res = reinterpret_cast<uint16_t*>(low + (kScan ? 0 : low_bytes(job.C, S)));
   const uint32_t seg_sh = seg_shift(job.C, NT), seg = 1u << seg_sh;
   const uint32_t nb = window_blocks(job.W);
   uint8_t* area = reinterpret_cast<uint8_t*>(res) + align_up(res_bytes(job.C, seg_sh), 16);
-  uint2* order = reinterpret_cast<uint2*>(area);
-  uint32_t* cnt32 = reinterpret_cast<uint32_t*>(order + max_ins(nb) + kUnroll);
-  uint32_t* shared = reinterpret_cast<uint32_t*>(area + area_bytes(job.C, seg_sh, nb));
-
-  stage_chunk<S>(job, stage);
-  __syncthreads();
-  bool exact = true;
-  if constexpr (S == 2) exact = take_low_bytes<NT>(stage, c, low, shared);
-  const SearchEnd end = search<S, NT>(stage, S == 2 ? low : stage, exact, c, job.W, job.MIN, res,
-                                      order, cnt32, shared, seg_sh);
-  if (end != kSearched) {
+  const uint32_t nsegC = segments(job.C, seg_sh);
+  uint32_t* shared;
+  if constexpr (kScan) {
+    shared = reinterpret_cast<uint32_t*>(area + align_up(nsegC * 16 + align_up(job.C, 64) / 8, 16));
+    stage_chunk<S>(job, stage);
     __syncthreads();
-    encode_chunk_spec<S, WC, kSinglePass, true>(job, lds, end == kConstant);
-    return;
+    scan_search<S, NT>(stage, c, job.W, job.MIN, res, seg_sh);
+    __syncthreads();
+  } else {
+    uint2* order = reinterpret_cast<uint2*>(area);
+    uint32_t* cnt32 = reinterpret_cast<uint32_t*>(order + max_ins(nb) + kUnroll);
+    shared = reinterpret_cast<uint32_t*>(area + area_bytes(job.C, seg_sh, nb));
+    stage_chunk<S>(job, stage);
+    __syncthreads();
+    bool exact = true;
+    if constexpr (S == 2) exact = take_low_bytes<NT>(stage, c, low, shared);
+    const SearchEnd end = search<S, NT>(stage, S == 2 ? low : stage, exact, c, job.W, job.MIN, res,
+                                        order, cnt32, shared, seg_sh);
+    if (end != kSearched) {
+      __syncthreads();
+      encode_chunk_spec<S, WC, kSinglePass, true>(job, lds, end == kConstant);
+      return;
+    }
   }
 
   // ---- parse
   const uint32_t nseg = (c + seg - 1) >> seg_sh;
-  const uint32_t nsegC = segments(job.C, seg_sh);
   uint2* T = reinterpret_cast<uint2*>(area);  // token starts, pointer starts
   uint32_t* pre = reinterpret_cast<uint32_t*>(T + nsegC);  // tokens | pointers << 16 before it
   uint32_t* exits = pre + nsegC;

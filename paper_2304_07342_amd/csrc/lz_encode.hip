@@ -254,6 +254,17 @@ __global__ __launch_bounds__(64 * enc::kEncodeWaves) void encode_scan_kernel(Fus
   enc::encode_chunk_scan<S>(job, lds);
 }
 
+// The same with the equal slots found 32 at a time and the parse split over the
+// lanes (see bucket_device.h), MIN >= 2.
+constexpr uint32_t kScanThreadsPerChunk = 256;
+template <int S>
+__global__ __launch_bounds__(kScanThreadsPerChunk) void encode_scan_bits_kernel(FusedArgs a) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ uint64_t item;
+  const enc::ChunkJob job = take_chunk(a, S, &item);
+  enc::bucket::encode_chunk<S, 4, kScanThreadsPerChunk, true, true>(job, lds);
+}
+
 template <int S, int WC>
 hipError_t launch_sw(const FusedArgs& a, uint32_t waves, hipStream_t s) {
   if constexpr (S <= 2) {
@@ -284,6 +295,12 @@ hipError_t launch_sw(const FusedArgs& a, uint32_t waves, hipStream_t s) {
 
 template <int S>
 hipError_t launch_s(const FusedArgs& a, uint32_t waves, hipStream_t s) {
+  if (a.policy == 1 && enc::bucket::takes_scan(a.C, S, a.MIN, kScanThreadsPerChunk)) {
+    hipLaunchKernelGGL((encode_scan_bits_kernel<S>), dim3((uint32_t)a.nchunks),
+                       dim3(kScanThreadsPerChunk),
+                       enc::bucket::scan_lds(a.C, S, kScanThreadsPerChunk), s, a);
+    return hipGetLastError();
+  }
   if (a.policy == 1) {
     const size_t lds = enc::scan_lds_bytes(a.C, S);
     hipLaunchKernelGGL((encode_scan_kernel<S>), dim3((uint32_t)a.nchunks), dim3(64 * waves), lds,
