@@ -6,9 +6,10 @@
 //   hist_kernel    per-workgroup byte histograms (32 bank-padded LDS
 //                  sub-histograms, 16-byte loads);
 //   build_kernel   one workgroup: sums the histograms, sorts (weight,
-//                  symbol) keys, runs Huffman's merge with two queues (sorted
-//                  leaves, internal nodes in creation order), limits the
-//                  lengths, assigns canonical codes, writes the code lengths;
+//                  symbol) keys, runs Huffman's merge (sorted leaves,
+//                  internal nodes in creation order) many joins a round,
+//                  limits the lengths, assigns canonical codes, writes the
+//                  code lengths;
 //   size_kernel    one wave per chunk: code bits of the chunk;
 //   scan_kernel    one workgroup: record offsets and the header;
 //   encode_kernel  one wave per chunk: bit offsets by a wave scan, codes
@@ -18,8 +19,8 @@
 //                       builds the lookup tables, scans the record sizes;
 //   decode_kernel       one lane per 128-symbol sub-block (32 lanes per
 //                       chunk): code words staged in LDS, a two-level
-//                       lookup table in LDS, symbols staged in LDS and
-//                       written out in consecutive 4-byte stores.
+//                       lookup table in LDS, each lane writing its symbols
+//                       with 16-byte stores.
 #include "huff_internal.h"
 #include "stream_device.h"
 #include "wave.h"
@@ -86,67 +87,156 @@ __global__ __launch_bounds__(256) void hist_kernel(EncArgs a) {
   a.partial[(uint64_t)blockIdx.x * 256 + tid] = sum;
 }
 
+// Lanes of the wave whose code has the same length as this lane's.
+__device__ __forceinline__ uint64_t same_length(uint32_t l) {
+  uint64_t same = ~0ull;
+#pragma unroll
+  for (uint32_t b = 0; b < 4; ++b) {
+    const uint64_t set = __ballot((l >> b) & 1u);
+    same &= (l >> b) & 1u ? set : ~set;
+  }
+  return same;
+}
+
+// Codes of each length among the symbols of each 64-symbol group: the rank
+// of a code among those of its length is a ballot inside its group and the
+// counts of the groups before it, where a loop over the symbols before it
+// took up to 256 dependent LDS reads.
+struct LengthCounts {
+  uint32_t n[4][16];
+
+  // Called by threads 0..255 with symbol tid's length; returns the rank in
+  // the group. `n` is zeroed before and read after a barrier.
+  __device__ __forceinline__ uint32_t add(uint32_t tid, uint32_t l) {
+    const uint64_t same = same_length(l);
+    const uint32_t r = __popcll(same & ((1ull << (tid & 63u)) - 1));
+    if (r == 0) n[tid >> 6][l] = __popcll(same);
+    return r;
+  }
+  __device__ __forceinline__ uint32_t before(uint32_t tid, uint32_t l) const {
+    uint32_t s = 0;
+#pragma unroll
+    for (uint32_t g = 0; g < 3; ++g) s += g < tid >> 6 ? n[g][l] : 0u;
+    return s;
+  }
+  __device__ __forceinline__ uint32_t total(uint32_t l) const {
+    return n[0][l] + n[1][l] + n[2][l] + n[3][l];
+  }
+};
+
 struct BuildLds {
   uint64_t w[256];    // weight by symbol (0 = absent)
-  uint64_t tmp[256];  // unsorted keys
+  uint64_t tmp[256];  // unsorted keys; a merge round's weights in order
   uint64_t key[256];  // weight << 8 | symbol, ascending; absent symbols last
   uint64_t iw[256];   // internal node weights in creation order
   uint16_t parent[512];
   uint16_t anc[256], dist[256];  // pointer jumping over internal nodes
   uint8_t len[256];
-  uint32_t count[16], next[16];
+  LengthCounts lengths;
+  uint32_t next[16];
   uint64_t total;       // sum of the weights
   uint32_t present, deepest, internal;
 };
 
-// Huffman's merge with two queues: sorted leaves, and internal nodes in
-// creation order (their weights never decrease). A leaf wins a tie (its index
-// is smaller). The four front candidates are read together, so each join
-// costs one LDS round trip. W is uint32_t when the weights sum below 2^31
-// (cheaper compares; used below 2^31 so that no weight equals the 32-bit
-// infinity), else uint64_t. Returns the number of internal nodes.
+// Huffman's merge by one wave: sorted leaves, and internal nodes in creation
+// order (their weights never decrease); a leaf wins a tie (its index is
+// smaller). One round joins every node that is at hand and no heavier than
+// the sum t of the two lightest: no node made in the round is lighter than t,
+// and one of weight t comes after the others of that weight, so joining them
+// two by two in ascending order is what one join after the other does. An odd
+// node at the end waits. t at least doubles every second round, so the
+// rounds follow the logarithm of the weights (about 20) where the joins one
+// by one were up to 255 LDS round trips (build_kernel on the LZSS stream of
+// 1 MiB or 128 MiB of codes: 64 us with one join at a time and the ranks
+// counted in a loop, 34 us so; what is left is the chain of rounds on one
+// wave). W is uint32_t when the weights sum
+// below 2^31 (cheaper compares; below 2^31 so that no weight equals the
+// 32-bit infinity), else uint64_t. Returns the number of internal nodes.
 template <typename W>
-__device__ uint32_t merge(BuildLds& sm, uint32_t m) {
+__device__ uint32_t merge(BuildLds& sm, uint32_t m, uint32_t lane) {
   const W kInf = (W)~0ull;
-  uint32_t li = 0, kf = 0, kc = 0;
-  for (uint32_t s = 0; s + 1 < m; ++s) {
+  W leaf[4];
+#pragma unroll
+  for (uint32_t q = 0; q < 4; ++q) {
+    const uint32_t x = 64 * q + lane;
+    leaf[q] = x < m ? (W)(sm.key[x] >> 8) : kInf;
+  }
+  uint32_t li = 0, kf = 0, kc = 0;  // first leaf and node at hand, nodes made
+  while (kc + 1 < m) {
+    W node[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t x = 64 * q + lane;
+      node[q] = x < kc ? (W)sm.iw[x] : kInf;
+    }
     const W l0 = li < m ? (W)(sm.key[li] >> 8) : kInf;
     const W l1 = li + 1 < m ? (W)(sm.key[li + 1] >> 8) : kInf;
     const W i0 = kf < kc ? (W)sm.iw[kf] : kInf;
     const W i1 = kf + 1 < kc ? (W)sm.iw[kf + 1] : kInf;
-    uint32_t na, nb;
-    W wa, wb;
-    if (l0 <= i0) {
-      na = li;
-      wa = l0;
-      if (l1 <= i0) {
-        nb = li + 1;
-        wb = l1;
-        li += 2;
-      } else {
-        nb = 256 + kf;
-        wb = i0;
-        li += 1;
-        kf += 1;
+    const W t = l0 <= i0 ? l0 + (l1 <= i0 ? l1 : i0) : i0 + (l0 <= i1 ? l0 : i1);
+    uint32_t le = 0, ie = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      le += __popcll(__ballot(leaf[q] <= t));
+      ie += __popcll(__ballot(node[q] <= t));
+    }
+    const uint32_t na = le - li, nb = ie - kf, k = na + nb;
+    // places in the merged order: a loop over the shorter list (what was
+    // joined before is no heavier than what is left, so whole counts less
+    // the joined ones are counts of what is left)
+    uint32_t pl[4], pn[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      pl[q] = 64 * q + lane - li;
+      pn[q] = 64 * q + lane - kf;
+    }
+    if (na <= nb) {
+      for (uint32_t x = li; x < le; ++x) {
+        const W v = (W)(sm.key[x] >> 8);
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+          c += __popcll(__ballot(node[q] < v));
+          pn[q] += v <= node[q] ? 1u : 0u;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) pl[q] += 64 * q + lane == x ? c - kf : 0u;
       }
     } else {
-      na = 256 + kf;
-      wa = i0;
-      if (l0 <= i1) {
-        nb = li;
-        wb = l0;
-        li += 1;
-        kf += 1;
-      } else {
-        nb = 256 + kf + 1;
-        wb = i1;
-        kf += 2;
+      for (uint32_t x = kf; x < ie; ++x) {
+        const W v = (W)sm.iw[x];
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+          c += __popcll(__ballot(leaf[q] <= v));
+          pl[q] += v < leaf[q] ? 1u : 0u;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) pn[q] += 64 * q + lane == x ? c - li : 0u;
       }
     }
-    sm.iw[kc] = (uint64_t)wa + wb;
-    sm.parent[na] = (uint16_t)(256 + kc);
-    sm.parent[nb] = (uint16_t)(256 + kc);
-    ++kc;
+    bool waits_node = false;
+    if (k & 1u)
+      waits_node = nb && (!na || (W)sm.iw[ie - 1] >= (W)(sm.key[le - 1] >> 8));
+    const uint32_t pairs = k / 2;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t x = 64 * q + lane;
+      if (x >= li && x < le && pl[q] < 2 * pairs) {
+        sm.tmp[pl[q]] = leaf[q];
+        sm.parent[x] = (uint16_t)(256 + kc + pl[q] / 2);
+      }
+      if (x >= kf && x < ie && pn[q] < 2 * pairs) {
+        sm.tmp[pn[q]] = node[q];
+        sm.parent[256 + x] = (uint16_t)(256 + kc + pn[q] / 2);
+      }
+    }
+    wave_sync();
+    for (uint32_t x = lane; x < pairs; x += 64) sm.iw[kc + x] = sm.tmp[2 * x] + sm.tmp[2 * x + 1];
+    wave_sync();
+    li = le - (k & 1u && !waits_node ? 1u : 0u);
+    kf = ie - (waits_node ? 1u : 0u);
+    kc += pairs;
   }
   return kc;
 }
@@ -196,23 +286,29 @@ __global__ __launch_bounds__(1024) void build_kernel(EncArgs a) {
     __syncthreads();
     if (tid < 256 && sm.w[tid]) atomicAdd(reinterpret_cast<unsigned long long*>(&sm.total),
                                           (unsigned long long)sm.w[tid]);
-    if (tid < 256) {
-      const uint64_t k = sm.tmp[tid];
+    {
+      // four adjacent threads count a quarter of the keys each
+      const uint64_t k = sm.tmp[tid >> 2];
       uint32_t r = 0;
-      for (uint32_t j = 0; j < 256; ++j) r += sm.tmp[j] < k;
-      sm.key[r] = k;
+#pragma unroll 16
+      for (uint32_t j = 0; j < 64; ++j) r += sm.tmp[4 * j + (tid & 3u)] < k;
+      r += __shfl_xor(r, 1);
+      r += __shfl_xor(r, 2);
+      if ((tid & 3u) == 0) sm.key[r] = k;
     }
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {
       uint32_t kc = 0;
       if (m == 1) {
-        sm.len[sm.key[0] & 255u] = 1;
+        if (tid == 0) sm.len[sm.key[0] & 255u] = 1;
       } else if (m > 1) {
         // 32-bit weights while every weight stays below the 32-bit infinity
-        kc = sm.total >> 31 ? merge<uint64_t>(sm, m) : merge<uint32_t>(sm, m);
+        kc = sm.total >> 31 ? merge<uint64_t>(sm, m, tid) : merge<uint32_t>(sm, m, tid);
       }
-      sm.internal = kc;
-      sm.deepest = m == 1 ? 1u : 0u;
+      if (tid == 0) {
+        sm.internal = kc;
+        sm.deepest = m == 1 ? 1u : 0u;
+      }
     }
     __syncthreads();
     // depths of the internal nodes by pointer jumping (8 rounds cover 255)
@@ -252,29 +348,23 @@ __global__ __launch_bounds__(1024) void build_kernel(EncArgs a) {
     __syncthreads();
   }
   // canonical codes
-  if (tid < 16) sm.count[tid] = 0;
+  if (tid < 64) sm.lengths.n[tid >> 4][tid & 15u] = 0;
   __syncthreads();
-  if (tid < 256 && sm.len[tid]) atomicAdd(&sm.count[sm.len[tid]], 1u);
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t c = 0;
-    sm.next[0] = 0;
-    for (uint32_t l = 1; l <= kLimit; ++l) {
-      c = (c + (l > 1 ? sm.count[l - 1] : 0u)) << 1;
-      sm.next[l] = c;
-    }
-  }
-  __syncthreads();
+  uint32_t l = 0, r = 0;
   if (tid < 256) {
-    const uint32_t l = sm.len[tid];
-    uint32_t code = 0;
-    if (l) {
-      uint32_t r = 0;
-      for (uint32_t t = 0; t < tid; ++t) r += sm.len[t] == l;
-      code = sm.next[l] + r;
-    }
-    a.codes[tid] = l << 16 | code;
+    l = sm.len[tid];
+    r = sm.lengths.add(tid, l);
   }
+  __syncthreads();
+  if (tid <= kLimit) {
+    // first code of length tid: every shorter code takes 2^(tid - length)
+    uint32_t c = 0;
+    for (uint32_t k = 1; k < tid; ++k) c += sm.lengths.total(k) << (tid - k);
+    sm.next[tid] = c;
+  }
+  __syncthreads();
+  if (tid < 256)
+    a.codes[tid] = l ? l << 16 | (sm.next[l] + sm.lengths.before(tid, l) + r) : 0u;
   if (tid < 128) a.out[64 + tid] = (uint8_t)(sm.len[2 * tid] | sm.len[2 * tid + 1] << 4);
   if (tid == 0) a.codes[256] = 0;
 }
@@ -436,63 +526,71 @@ __global__ __launch_bounds__(64 * kEncWaves) void encode_kernel(EncArgs a) {
 
 // ---- decompression ---------------------------------------------------------
 
-__device__ inline uint64_t get_le(const uint8_t* p, int bytes) {
-  uint64_t v = 0;
-  for (int k = bytes - 1; k >= 0; --k) v = v << 8 | p[k];
-  return v;
-}
-
 struct PrepLds {
   DecTables t;
-  uint8_t len[256];
-  uint32_t kraft, present, bad;
+  LengthCounts lengths;
+  uint32_t bad;
   uint64_t scratch[1024 / 64 + 1];
 };
 
+// One workgroup, so a chain of latencies bounds it: the header comes in 64
+// bytes at once (checked byte by byte it was up to 24 dependent loads) and the
+// ranks from ballots; 1 MiB of codes' stream 13.4 -> 8.2 us with the loop over
+// the symbols gone.
 __global__ __launch_bounds__(1024) void dec_prepare_kernel(DecArgs a) {
   __shared__ PrepLds sm;
   const uint32_t tid = threadIdx.x;
   DecTables& T = sm.t;
   if (tid == 0) {
-    const uint8_t* h = a.in;
-    bool ok = a.in_bytes >= kPre && h[0] == 'G' && h[1] == 'L' && h[2] == 'H' && h[3] == '1' &&
-              get_le(h + 4, 2) == 1 && h[6] == kLimit && h[7] == 0 && get_le(h + 8, 4) == kChunk &&
-              get_le(h + 12, 4) == kSub;
-    for (uint32_t b = 40; ok && b < 64; ++b) ok = h[b] == 0;
+    bool ok = a.in_bytes >= kPre;
     if (ok) {
-      T.n = get_le(h + 16, 8);
-      T.N = get_le(h + 24, 8);
-      ok = get_le(h + 32, 8) == a.in_bytes && T.N == chunks(T.n) && T.N <= (a.in_bytes - kPre) / 4;
+      // the 64-byte header in four loads: magic, version, code length limit
+      // and zero | chunk and sub-block symbols | n, chunks | stream bytes |
+      // zeros
+      const uint64_t* h = reinterpret_cast<const uint64_t*>(a.in);
+      uint64_t v[8];
+#pragma unroll
+      for (uint32_t b = 0; b < 8; ++b) v[b] = h[b];
+      ok = v[0] == (0x31484C47ull | 1ull << 32 | (uint64_t)kLimit << 48) &&
+           v[1] == (kChunk | (uint64_t)kSub << 32) && (v[5] | v[6] | v[7]) == 0;
+      T.n = v[2];
+      T.N = v[3];
+      ok = ok && v[4] == a.in_bytes && T.N == chunks(T.n) && T.N <= (a.in_bytes - kPre) / 4;
     }
     T.status = ok ? kOk : kCorrupt;
-    sm.kraft = 0;
-    sm.present = 0;
     sm.bad = 0;
   }
-  if (tid < 16) T.count[tid] = 0;
+  if (tid < 64) sm.lengths.n[tid >> 4][tid & 15u] = 0;
   __syncthreads();
+  uint32_t len = 0, rank = 0;
   if (T.status == kOk && tid < 256) {
-    const uint32_t l = (a.in[64 + tid / 2] >> (4 * (tid & 1u))) & 15u;
-    sm.len[tid] = (uint8_t)l;
-    if (l) {
-      atomicAdd(&sm.present, 1u);
-      atomicAdd(&T.count[l], 1u);
-      atomicAdd(&sm.kraft, 1u << (kLimit - l));
+    len = (a.in[64 + tid / 2] >> (4 * (tid & 1u))) & 15u;
+    rank = sm.lengths.add(tid, len);
+  }
+  __syncthreads();
+  if (tid <= kLimit && T.status == kOk) {
+    // first code and rank of length tid, from the codes shorter than it
+    uint32_t c = 0, r = 0;
+    for (uint32_t k = 1; k < tid; ++k) {
+      const uint32_t m = sm.lengths.total(k);
+      c += m << (tid - k);
+      r += m;
+    }
+    T.first[tid] = c;
+    T.rank0[tid] = r;
+    T.count[tid] = tid ? sm.lengths.total(tid) : 0u;
+    if (tid == kLimit) {
+      const uint32_t longest = sm.lengths.total(kLimit);
+      const uint32_t present = r + longest, kraft = c + longest;
+      const bool code_ok = T.n == 0 ? present == 0
+                                    : (present == 1 ? sm.lengths.total(1) == 1 : kraft == (1u << kLimit));
+      if (!code_ok) sm.bad = 1;
     }
   }
   __syncthreads();
-  if (tid == 0 && T.status == kOk) {
-    const bool code_ok = T.n == 0 ? sm.present == 0
-                                  : (sm.present == 1 ? T.count[1] == 1 : sm.kraft == (1u << kLimit));
-    if (!code_ok) T.status = kCorrupt;
-    uint32_t c = 0, r = 0;
-    for (uint32_t l = 1; l <= kLimit; ++l) {
-      c = (c + (l > 1 ? T.count[l - 1] : 0u)) << 1;
-      T.first[l] = c;
-      T.rank0[l] = r;
-      r += T.count[l];
-    }
-    T.first[0] = T.rank0[0] = 0;
+  if (tid == 0 && sm.bad) {
+    T.status = kCorrupt;
+    sm.bad = 0;
   }
   __syncthreads();
   if (T.status != kOk) {
@@ -503,12 +601,7 @@ __global__ __launch_bounds__(1024) void dec_prepare_kernel(DecArgs a) {
     }
     return;
   }
-  if (tid < 256 && sm.len[tid]) {
-    const uint32_t l = sm.len[tid];
-    uint32_t r = 0;
-    for (uint32_t t = 0; t < tid; ++t) r += sm.len[t] == l;
-    T.by_rank[T.rank0[l] + r] = (uint8_t)tid;
-  }
+  if (tid < 256 && len) T.by_rank[T.rank0[len] + sm.lengths.before(tid, len) + rank] = (uint8_t)tid;
   __syncthreads();
   // two-level table, every entry decoded on its own thread: an 11-bit prefix
   // holds the code of length <= 11 it starts with; prefixes from first(12) / 2
@@ -602,41 +695,43 @@ __global__ __launch_bounds__(1024) void dec_prepare_kernel(DecArgs a) {
   for (uint32_t k = tid; k < sizeof(DecTables) / 4; k += 1024) dst[k] = src[k];
 }
 
-constexpr uint32_t kDecWaves = 4;                  // waves per decode workgroup
-constexpr uint32_t kInStageWords = 1024;           // code words staged per chunk (8 bits/symbol)
-constexpr uint32_t kStageSub = kSub + 4;           // LDS bytes per decoded sub-block (bank padding)
-constexpr uint32_t kStageChunk = kSubs * kStageSub + 4;
-constexpr uint32_t kDecodeBlocks = 256 * 2;
-
-struct DecWaveLds {
-  uint32_t in[2][kInStageWords];       // code words of the wave's two chunks
-  uint32_t out[2][kStageChunk / 4];    // their decoded bytes
-};
+constexpr uint32_t kDecWaves = 4;                // waves per decode workgroup
+constexpr uint32_t kInStageWords = 1024;         // code words staged per chunk (8 bits/symbol)
+constexpr uint32_t kMaxDecodeBlocks = 16384;
 
 struct DecLds {
-  uint16_t lut[1u << kLutBits];
+  alignas(8) uint16_t lut[1u << kLutBits];
   uint16_t lut2[kMaxSubtables * 16];
-  DecWaveLds w[kDecWaves];
+  uint32_t in[kDecWaves][2][kInStageWords];  // code words of each wave's two chunks
 };
 
 struct DecCode {
   const uint16_t* lut;
   const uint16_t* lut2;
+  uint32_t long0;  // first 15-bit window of the codes longer than 11 bits
+};
+
+// 16 bytes at a 4-byte boundary (chunks start 4096 bytes apart in an output
+// that is 4-byte aligned).
+struct __attribute__((packed, aligned(4))) Quad {
+  uint32_t v[4];
 };
 
 // Decodes the `cnt` symbols of one sub-block starting at bit `start` of the
-// chunk's code words `wds` (nwords >= 1 of them) into `out32`; returns the
-// bit position after them, or ~0u if one of them matches no code. Every lane
-// runs all 128 steps, so the loop is uniform across the wave: steps past
-// `cnt` decode whatever bits follow and are ignored (they only write into
-// this sub-block's own stage slot). Word reads are clamped to the last word
-// instead of branching: bits past a sub-block's end never decide whether it
-// ends exactly at its end bit. The bit buffer is refilled once per pair of
-// symbols (after a refill it holds at least 32 bits; two codes take at most
-// 30). Codes of up to 11 bits take one table read, longer ones a second one.
+// chunk's code words `wds` (nwords >= 1 of them) and writes them at `dst`;
+// returns the bit position after them, or ~0u if one of them matches no code.
+// Every lane runs all 128 steps, so the loop is uniform across the wave:
+// steps past `cnt` decode whatever bits follow and are not written. Word
+// reads are clamped to the last word instead of branching: bits past a
+// sub-block's end never decide whether it ends exactly at its end bit. The
+// bit buffer is refilled once per pair of symbols (after a refill it holds at
+// least 32 bits; two codes take at most 30). The chain from one code to the
+// next is one table read: the second-level entry of a longer code is at a
+// place that the window alone gives (those codes are the last ones, so their
+// windows are consecutive), and both tables are read at once.
 template <typename WordPtr>
 __device__ __forceinline__ uint32_t decode_sub(const DecCode& dc, WordPtr wds, uint32_t nwords,
-                                               uint32_t start, uint32_t cnt, uint32_t* out32) {
+                                               uint32_t start, uint32_t cnt, uint8_t* dst) {
   const uint32_t last = nwords - 1;
   uint32_t wi = start >> 5;
   const uint32_t w0 = wds[wi < last ? wi : last], w1 = wds[wi + 1 < last ? wi + 1 : last];
@@ -644,58 +739,83 @@ __device__ __forceinline__ uint32_t decode_sub(const DecCode& dc, WordPtr wds, u
   uint64_t buf = ((uint64_t)w0 << 32 | w1) << (start & 31u);
   uint32_t avail = 64 - (start & 31u), p = start, p_end = start;
   bool bad = false;
-  for (uint32_t j = 0; j < kSub; j += 4) {
-    uint32_t acc = 0;
+  for (uint32_t j = 0; j < kSub; j += 16) {
+    Quad q;
 #pragma unroll
-    for (uint32_t u = 0; u < 4; ++u) {
-      if ((u & 1u) == 0) {
-        const uint32_t w = wds[wi < last ? wi : last];
-        const bool take = avail < 32;
-        buf |= take ? (uint64_t)w << (32 - avail) : 0ull;
-        wi += take ? 1u : 0u;
-        avail += take ? 32u : 0u;
+    for (uint32_t v = 0; v < 4; ++v) {
+      uint32_t acc = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        if ((u & 1u) == 0) {
+          const uint32_t w = wds[wi < last ? wi : last];
+          const bool take = avail < 32;
+          buf |= take ? (uint64_t)w << (32 - avail) : 0ull;
+          wi += take ? 1u : 0u;
+          avail += take ? 32u : 0u;
+        }
+        const uint32_t peek = (uint32_t)(buf >> (64 - kLimit));
+        uint32_t k2 = peek - dc.long0;
+        k2 = k2 < kMaxSubtables * 16 ? k2 : 0u;
+        const uint32_t e1 = dc.lut[peek >> (kLimit - kLutBits)];
+        const uint32_t e2 = dc.lut2[k2];
+        const uint32_t e = e1 & 0x8000u ? e2 : e1;
+        uint32_t l = e >> 8;
+        const uint32_t sym = e & 0xFFu;
+        if (l == 0) bad = bad || j + 4 * v + u < cnt;
+        l = l ? l : 1u;
+        buf <<= l;
+        avail -= l;
+        p += l;
+        p_end = j + 4 * v + u + 1 == cnt ? p : p_end;
+        acc |= sym << (8 * u);
       }
-      const uint32_t peek = (uint32_t)(buf >> (64 - kLimit));
-      uint32_t e = dc.lut[peek >> (kLimit - kLutBits)];
-      if (e & 0x8000u) e = dc.lut2[(e & 0x7FFFu) * 16 + (peek & 15u)];
-      uint32_t l = e >> 8;
-      const uint32_t sym = e & 0xFFu;
-      if (l == 0) bad = bad || j + u < cnt;
-      l = l ? l : 1u;
-      buf <<= l;
-      avail -= l;
-      p += l;
-      p_end = j + u + 1 == cnt ? p : p_end;
-      acc |= sym << (8 * u);
+      q.v[v] = acc;
     }
-    out32[j >> 2] = acc;
+    if (j + 16 <= cnt) {
+      *reinterpret_cast<Quad*>(dst + j) = q;
+    } else {
+#pragma unroll
+      for (uint32_t b = 0; b < 16; ++b)
+        if (j + b < cnt) dst[j + b] = (uint8_t)(q.v[b / 4] >> (8 * (b & 3u)));
+    }
   }
   return bad ? ~0u : p_end;
 }
 
 // Each wave takes two chunks at a time (32 lanes each, one lane per
 // 128-symbol sub-block): it stages the chunks' code words in LDS with
-// coalesced loads, decodes every sub-block from LDS into an LDS stage, and
-// writes the chunks out with consecutive 4-byte stores. Only the wave
-// synchronises; a chunk with more than 4 KiB of code words (above 8 bits per
-// symbol) is decoded from global memory instead.
+// coalesced loads and decodes every sub-block from LDS; each lane writes its
+// own 128 bytes with 16-byte stores. Only the wave synchronises; a chunk with
+// more than 4 KiB of code words (above 8 bits per symbol) is decoded from
+// global memory instead.
+// Bound by the latency of the chain table read -> shift -> table read, so by
+// the waves at hand: with the decoded symbols staged in LDS too, 8 waves fit
+// a compute unit (69 MB of LZSS stream: 146 us); without that stage 12 fit as
+// workgroups of four (77 us), 16 as workgroups of eight (89 us) or of sixteen
+// (slower still): the smaller groups are handed out more evenly.
 __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(DecArgs a) {
   __shared__ DecLds sm;
   const DecTables* T = a.tab;
   if (T->status != kOk) return;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint64_t n = T->n, N = T->N;
-  for (uint32_t k = tid; k < (1u << kLutBits); k += 64 * kDecWaves) sm.lut[k] = T->lut[k];
-  for (uint32_t k = tid; k < kMaxSubtables * 16; k += 64 * kDecWaves) sm.lut2[k] = T->lut2[k];
+  if ((uint64_t)blockIdx.x * kDecWaves * 2 >= N) return;
+  {
+    // the two tables are adjacent in both places
+    const uint2* src = reinterpret_cast<const uint2*>(T->lut);
+    uint2* dst = reinterpret_cast<uint2*>(sm.lut);
+    constexpr uint32_t kPairs = (sizeof(sm.lut) + sizeof(sm.lut2)) / 8;
+    for (uint32_t k = tid; k < kPairs; k += 64 * kDecWaves) dst[k] = src[k];
+  }
   DecCode dc;
   dc.lut = sm.lut;
   dc.lut2 = sm.lut2;
+  dc.long0 = (T->first[kLutBits + 1] >> 1) << (kLimit - kLutBits);
   __syncthreads();
   const uint32_t* bits_tab = reinterpret_cast<const uint32_t*>(a.in + kPre);
   const uint64_t rec_base = kPre + 4 * N;
-  DecWaveLds& w = sm.w[wave];
   const uint32_t half = lane >> 5, k = lane & 31u;
-  uint8_t* out8 = reinterpret_cast<uint8_t*>(w.out[half]);
+  uint32_t* in = sm.in[wave][half];
   bool bad = false;
   for (uint64_t g = (uint64_t)blockIdx.x * kDecWaves + wave; 2 * g < N; g += (uint64_t)gridDim.x * kDecWaves) {
     const uint64_t i = 2 * g + half;
@@ -713,7 +833,8 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(DecArgs a) {
     }
     const bool staged = nwords <= kInStageWords;
     if (live && staged)
-      for (uint32_t q = k; q < nwords; q += 32) w.in[half][q] = wds[q];
+#pragma unroll 8
+      for (uint32_t q = k; q < nwords; q += 32) in[q] = wds[q];
     wave_sync();
     if (live && k < nsub) {
       const uint16_t* o16 = reinterpret_cast<const uint16_t*>(rec);
@@ -724,24 +845,12 @@ __global__ __launch_bounds__(64 * kDecWaves) void decode_kernel(DecArgs a) {
       if (k + 1 == nsub && (nsub & 1u) && o16[nsub] != 0) ok = false;
       if (ok && k + 1 == nsub && (bits & 31u) && (wds[nwords - 1] << (bits & 31u)) != 0) ok = false;
       if (ok) {
-        uint32_t* out32 = reinterpret_cast<uint32_t*>(out8 + k * kStageSub);
-        const uint32_t p = staged ? decode_sub(dc, (const uint32_t*)w.in[half], nwords, start, cnt, out32)
-                                  : decode_sub(dc, wds, nwords, start, cnt, out32);
+        uint8_t* dst = a.out + i * kChunk + kSub * k;
+        const uint32_t p = staged ? decode_sub(dc, (const uint32_t*)in, nwords, start, cnt, dst)
+                                  : decode_sub(dc, wds, nwords, start, cnt, dst);
         ok = p == end;
       }
       bad = bad || !ok;
-    }
-    wave_sync();
-    if (live) {
-      uint8_t* dst = a.out + i * kChunk;
-      for (uint32_t p = 4 * k; p < c; p += 4 * 32) {
-        const uint32_t v = *reinterpret_cast<const uint32_t*>(out8 + (p / kSub) * kStageSub + p % kSub);
-        if (p + 4 <= c) {
-          *reinterpret_cast<uint32_t*>(dst + p) = v;
-        } else {
-          for (uint32_t b = 0; p + b < c; ++b) dst[p + b] = (uint8_t)(v >> (8 * b));
-        }
-      }
     }
     wave_sync();
   }
@@ -763,7 +872,14 @@ hipError_t launch_compress(const EncArgs& a, hipStream_t s) {
 
 hipError_t launch_decompress(const DecArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(dec_prepare_kernel, dim3(1), dim3(1024), 0, s, a);
-  hipLaunchKernelGGL(decode_kernel, dim3(kDecodeBlocks), dim3(64 * kDecWaves), 0, s, a);
+  // a workgroup for every 2 * kDecWaves chunks that the stream and the output
+  // can hold; those past the stream's own count leave at once
+  uint64_t most = a.in_bytes > kPre ? (a.in_bytes - kPre) / 4 : 0;
+  if (most > a.capacity / kChunk + 1) most = a.capacity / kChunk + 1;
+  uint64_t blocks = (most + 2 * kDecWaves - 1) / (2 * kDecWaves);
+  if (blocks > kMaxDecodeBlocks) blocks = kMaxDecodeBlocks;
+  if (blocks)
+    hipLaunchKernelGGL(decode_kernel, dim3((uint32_t)blocks), dim3(64 * kDecWaves), 0, s, a);
   return hipGetLastError();
 }
 
