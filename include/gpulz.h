@@ -102,14 +102,18 @@ gpulz_status gpulz_compress_workspace_size(uint64_t nbytes, uint32_t symbol_byte
  *                 unspecified); GPULZ_ERR_HIP if a device-side wait of the
  *                 record-offset look-back gave up (not expected in use)
  *   d_workspace   at least gpulz_compress_workspace_size bytes
- * The call launches one small preparation kernel and then one chunk-encoder
- * launch per 2^22 chunks: every chunk finds its record offset by decoupled
- * look-back over the sizes its predecessors publish (the global prefix sum
- * of section 3.2.2) and writes its table entry and record once, at the final
- * place (section 3.3.4's compaction needs no pass of its own). Inputs of
+ * For 1- and 2-byte symbols the call launches one small preparation kernel
+ * and then one chunk-encoder launch per 2^22 chunks: every chunk finds its
+ * record offset by decoupled look-back over the sizes its predecessors publish
+ * (the global prefix sum of section 3.2.2) and writes its table entry and
+ * record once, at the final place (section 3.3.4's compaction needs no pass of
+ * its own). For 4- and 8-byte symbols with min_match >= 2 and chunks of at most
+ * 32 KiB it launches chunk sizing per 2^22 chunks, a scan of the sizes (above
+ * 1024 chunks) and a kernel that writes the table and the records. Inputs of
  * more than 2^27 chunks give GPULZ_ERR_UNSUPPORTED.
- * The chunk encoder runs with the waves_per_chunk of the width's defaults
- * (gpulz_default_params); that changes speed, never the bytes.
+ * waves_per_chunk of the width's defaults (gpulz_default_params) is used by
+ * the general encoder only (min_match 1, larger minimum matches of narrow
+ * symbols, larger chunks); it changes speed, never the bytes.
  * Asynchronous on `stream` (0 = null stream). Same bytes as any other
  * conforming producer for the same input and parameters. Calls that overlap
  * must use distinct workspaces. */
@@ -232,8 +236,9 @@ gpulz_status gpulz_decompress_noalloc(const void* d_in, uint64_t in_bytes, void*
 /* ---- batches ------------------------------------------------------------
  * Many buffers, each with its own size and symbol width, compressed or
  * decompressed by one fixed sequence of launches on one stream (a plan
- * kernel, one persistent kernel that takes (buffer, chunk) work items from a
- * device-side ticket, a per-buffer scan, a compaction), with no host round
+ * kernel, one persistent kernel per symbol width that takes (buffer, chunk)
+ * work items from a device-side ticket, a per-buffer scan, a compaction; to
+ * decompress, one kernel by workgroups and one by waves), with no host round
  * trip and no allocation, so the call can be captured in a HIP graph and
  * replayed with new array contents. Each buffer's output is a standalone
  * stream, byte-identical to gpulz_compress / gpulz_decompress on that buffer
@@ -242,8 +247,10 @@ gpulz_status gpulz_decompress_noalloc(const void* d_in, uint64_t in_bytes, void*
  */
 
 /* Parameters for one symbol width; zero fields take the library default for
- * that width. waves_per_chunk is the workgroup size of the chunk encoder in
- * wavefronts (1, 2 or 4); one batch launch uses the largest value given. */
+ * that width. waves_per_chunk is the workgroup size of the general chunk
+ * encoder in wavefronts (1, 2 or 4); one batch launch uses the largest value
+ * given. The encoders that parameters with min_match = 2 usually take have
+ * workgroup sizes of their own. */
 typedef struct {
   uint32_t chunk_symbols;
   uint32_t window;
@@ -363,8 +370,8 @@ gpulz_status gpulz_huff_decompress(const void* d_in, uint64_t in_bytes, void* d_
 /* Kernel timing for benchmarks. While enabled, every gpulz_compress and
  * gpulz_decompress call records a pair of HIP events on its own stream
  * around each kernel it launches, so the times cover exactly those kernels.
- * Kernel ids: 0 chunk encode (with the look-back and the record write-out),
- * 1 compress preparation, 2 not used, 3 decode prepare (header check + table
+ * Kernel ids: 0 chunk encode (with the look-back or the scan, and the record
+ * write-out), 1 compress preparation, 2 not used, 3 decode prepare (header check + table
  * scan), 4 chunk decode, 5 a whole
  * gpulz_compress_batch call, 6 a whole gpulz_decompress_batch call, 7 a
  * whole gpulz_huff_compress call, 8 a whole gpulz_huff_decompress call.

@@ -385,23 +385,6 @@ struct BlockLds {
   uint32_t scratch[16];
 };
 
-// Block-wide exclusive scan (sum) of one u32 per thread; `total` gets the sum.
-__device__ inline uint32_t block_excl_scan_u32(uint32_t v, uint32_t* scratch, uint32_t& total) {
-  const uint32_t lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const uint32_t incl = wave_incl_scan(v);
-  if (lane == 63) scratch[wid] = incl;
-  __syncthreads();
-  uint32_t before = 0;
-  total = 0;
-  for (uint32_t w = 0; w < nw; ++w) {
-    const uint32_t x = scratch[w];
-    before += w < wid ? x : 0u;
-    total += x;
-  }
-  __syncthreads();
-  return before + incl - v;
-}
-
 // Block-wide maximum and sum of one u32 each per thread, and any of a flag.
 __device__ inline void block_reduce(uint32_t& mx, uint32_t& sum, bool& any, uint32_t* scratch) {
   const uint32_t lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;

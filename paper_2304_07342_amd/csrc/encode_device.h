@@ -1208,49 +1208,37 @@ __device__ inline uint64_t lookback(uint64_t* desc, uint64_t i, uint64_t agg) {
   uint64_t excl = 0;
   uint64_t j = i;  // chunks [0, j) not yet summed
   uint32_t polls = 0;
-  bool failed = false, done = false, far = false;
-  while (!done) {
-    // lane l reads chunk j - 1 - l; lanes past chunk 0 read an empty prefix.
-    // Once the nearest 64 are all published, 256 a poll
-    uint64_t v[4];
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) {
-      const uint64_t l = lane + 64 * k;
-      v[k] = k == 0 || far ? (l < j ? desc_load(desc + (j - 1 - l)) : kDescPrefix) : 0ull;
+  bool failed = false;
+  for (;;) {
+    // lane l reads chunk j - 1 - l; lanes past chunk 0 read an empty prefix
+    const uint64_t v = lane < j ? desc_load(desc + (j - 1 - lane)) : kDescPrefix;
+    const uint32_t st = (uint32_t)(v >> 62);
+    const uint64_t ready = ballot(st != 0);
+    const uint64_t pref = ballot(st == 2);
+    // lanes 0 .. run-1 are all published
+    const uint32_t run = ready == ~0ull ? 64u : (uint32_t)__builtin_ctzll(~ready);
+    const uint64_t pm = pref & (run == 64u ? ~0ull : ((1ull << run) - 1ull));
+    if (pm) {
+      const uint32_t pl = (uint32_t)__builtin_ctzll(pm);
+      // single-chunk sizes (lanes below pl) are far below 2^32 each
+      excl += readlane(wave_incl_scan(lane < pl ? (uint32_t)v : 0u), 63);
+      const uint64_t pv = ((uint64_t)readlane((uint32_t)(v >> 32), pl) << 32 |
+                           readlane((uint32_t)v, pl)) & kDescValue;
+      failed = pv == kDescValue;
+      excl += pv;
+      break;
     }
-    bool moved = false;
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k) {
-      const uint32_t st = (uint32_t)(v[k] >> 62);
-      const uint64_t ready = ballot(st != 0);
-      const uint64_t pref = ballot(st == 2);
-      // lanes 0 .. run-1 are all published
-      const uint32_t run = ready == ~0ull ? 64u : (uint32_t)__builtin_ctzll(~ready);
-      const uint64_t pm = pref & (run == 64u ? ~0ull : ((1ull << run) - 1ull));
-      const uint32_t n = pm ? (uint32_t)__builtin_ctzll(pm) : run;  // sizes to add
-      // single-chunk sizes are far below 2^32 each
-      if (n) excl += readlane(wave_incl_scan(lane < n ? (uint32_t)v[k] : 0u), 63);
-      if (pm) {
-        const uint64_t pv = ((uint64_t)readlane((uint32_t)(v[k] >> 32), n) << 32 |
-                             readlane((uint32_t)v[k], n)) & kDescValue;
-        failed = pv == kDescValue;
-        excl += pv;
-        done = true;
-        break;
-      }
+    if (run) {
+      excl += readlane(wave_incl_scan(lane < run ? (uint32_t)v : 0u), 63);
       j -= run;
-      moved |= run != 0;
-      if (run != 64) break;
-    }
-    if (done) break;
-    far = moved;
-    if (moved) {
       polls = 0;
-    } else if (++polls > kLookbackPolls) {
-      failed = done = true;
-    } else {
-      __builtin_amdgcn_s_sleep(1);
+      continue;
     }
+    if (++polls > kLookbackPolls) {
+      failed = true;
+      break;
+    }
+    __builtin_amdgcn_s_sleep(4);
   }
   if (failed) excl = kDescValue;
   if (lane == 0) desc_store(desc + i, kDescPrefix | (failed ? kDescValue : excl + agg));

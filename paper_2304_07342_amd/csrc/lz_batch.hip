@@ -7,17 +7,17 @@
 //   encode   one persistent launch per symbol width: each workgroup takes
 //            (buffer, chunk) work items of that width from the width's atomic
 //            ticket, so thousands of uneven buffers balance at chunk grain,
-//            and every width runs with its own waves per chunk and LDS size
-//            (dense widths parse fastest with many 1-wave workgroups);
+//            and every width runs its own encoder, workgroup and LDS size;
 //   scan     one workgroup per buffer prefix-sums its chunks' record sizes
 //            and writes its header, size and status;
 //   scatter  grid-stride over all chunks: table entry and record into the
-//            buffer's stream.
+//            buffer's stream, wide chunks without pointers from the input.
 // Every buffer's stream is byte-identical to gpulz_compress on that buffer.
 //
 // Decompression: per-buffer header checks, a prefix sum over buffers of
 // chunk counts and record-offset groups, one workgroup per buffer for its
-// table, then a persistent decoder over all chunks.
+// table, then a persistent decoder over all chunks (two launches: workgroups, and
+// for the narrow buffers of large batches waves).
 #include "decode_device.h"
 #include "bucket_device.h"
 #include "wide_device.h"
@@ -321,7 +321,8 @@ __global__ __launch_bounds__(256) void batch_dec_table_kernel(BatchDecArgs a) {
 }
 
 // Batches of more chunks than this have those of 1- and 2-byte symbols decoded
-// by one wave per chunk (see lz_decode.hip).
+// by one wave per chunk: the two decoders and their crossover are those of a
+// single stream (lz_decode.hip has both sides' times).
 constexpr uint64_t kFewBatchChunks = 1536;
 __device__ __forceinline__ bool narrow_by_waves(const BatchDecArgs& a) {
   return a.ctrl->T_all > kFewBatchChunks;

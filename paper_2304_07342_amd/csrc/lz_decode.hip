@@ -140,7 +140,15 @@ hipError_t launch_decode_chunks(const DecodeArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(decode_kernel, dim3(kDecodeBlocks), dim3(dec::kDecThreads), 0, s, a);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(decode_wave_kernel, dim3(kWaveBlocks), dim3(kWaveThreads), 0, s, a);
+  // a chunk takes at least 10 stream bytes (table entry, a flag byte and a
+  // payload byte): small streams cannot have the many chunks of the wave
+  // decoder, or not enough for all its workgroups
+  const uint64_t most = a.in_bytes > kHeaderBytes ? (a.in_bytes - kHeaderBytes) / 10 : 0;
+  if (most <= kFewChunks) return hipSuccess;
+  constexpr uint32_t kPer = kWaveThreads / 64;
+  const uint64_t blocks = (most + kPer - 1) / kPer;
+  hipLaunchKernelGGL(decode_wave_kernel, dim3((uint32_t)(blocks < kWaveBlocks ? blocks : kWaveBlocks)),
+                     dim3(kWaveThreads), 0, s, a);
   return hipGetLastError();
 }
 

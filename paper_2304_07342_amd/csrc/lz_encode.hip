@@ -1,23 +1,30 @@
-// Single-buffer compression in one pass over the records: a preparation
-// kernel, then the chunk encoders (one workgroup per chunk; see
-// encode_device.h for the steps), which take chunk ids from an atomic ticket,
-// find their record offsets by decoupled look-back and write the table entry
-// and record straight into the stream. Match policy 0 (exact longest match)
-// and 1 (the paper's single window pass).
+// Single-buffer compression, match policy 0 (exact longest match) and 1 (the
+// paper's single window pass), in one of two forms:
+//   1- and 2-byte symbols, policy 1, and what the second form does not take: a
+//     preparation kernel, then the chunk encoders (one workgroup per chunk),
+//     which take chunk ids from an atomic ticket, find their record offsets by
+//     decoupled look-back and write the table entry and record straight into
+//     the stream;
+//   4- and 8-byte symbols, MIN >= 2, chunks of at most 32 KiB: chunk sizes in
+//     any order, a scan of them, then the records.
+// The encoders' steps are in bucket_device.h (narrow symbols, policy 1),
+// wide_device.h and encode_device.h (the general ones).
 #include "bucket_device.h"
 #include "wide_device.h"
 
 namespace gpulz {
 namespace {
 
-// Launches of at most this many chunks take the split-parse encoder (measured
-// crossovers on 256 CUs: about 1.5-2.5 K chunks for 1- and 2-byte symbols,
-// 512 for 4-byte ones).
+// Where the general encoders are taken, launches of at most this many chunks
+// split the parse (measured crossovers on 256 CUs: about 1.5-2.5 K chunks for
+// 1- and 2-byte symbols, 512 for 4-byte ones).
 constexpr uint64_t kSpecMaxChunksNarrow = 1024;  // S <= 2
 constexpr uint64_t kSpecMaxChunksWide = 512;     // S >= 4
 // Launches of at most this many chunks take the bucket encoder with 16 waves
-// per chunk instead of 4.
-constexpr uint64_t kBucketFewChunks = 512;
+// per chunk instead of 4: one such workgroup fits each of the 256 CUs at a
+// time. uint16 codes (C 2048, W 128), 16 waves and 4: 256 chunks 35.7 and
+// 41.4 us, 512 chunks 66.1 and 48.8, 1024 chunks 124.9 and 63.2.
+constexpr uint64_t kBucketFewChunks = 256;
 
 __global__ __launch_bounds__(256) void prep_kernel(FusedArgs a) {
   const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -99,7 +106,8 @@ __global__ __launch_bounds__(64 * enc::kSpecWaves) void encode_spec_kernel(Fused
 }
 
 // 1- and 2-byte symbols with MIN >= 2: candidates from 2-symbol buckets, NT
-// threads per chunk (see bucket_device.h).
+// threads per chunk (see bucket_device.h). At least 6 waves per SIMD: the
+// search waits on LDS reads, and its 69 registers leave room for 7.
 template <int S, int WC, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6)))
 void encode_bucket_kernel(FusedArgs a) {
@@ -131,7 +139,10 @@ __device__ __forceinline__ WideView wide_view(const FusedArgs& a) {
   return v;
 }
 constexpr uint32_t kWideGroup = 64;
-// Launches of at most this many chunks need no scan launch.
+// Launches of at most this many chunks need no scan launch: every writing
+// workgroup sums the sizes itself. float32 field (C 4096, W 256), without the
+// launch and with it: 256 chunks 38.4 and 42.3 us, 1024 chunks 43.5 and 47.4,
+// 2048 chunks 53.9 and 55.7, 4096 chunks 77.3 and 73.5.
 constexpr uint64_t kWideSumChunks = 1024;
 __device__ __forceinline__ uint32_t wide_bytes(uint32_t size) {
   return (size & 0xFFFFu) + (size >> 16 & 0x7FFFu);

@@ -20,7 +20,10 @@ namespace wide {
 // staged, and their candidates searched exactly. Candidates of any distance are
 // kept (the search decides), so the window does not matter here.
 //
-// Bound by instruction issue: about 30 vector instructions and 2 LDS accesses per
+// 256 MiB float32 field (C 4096, W 256): 508 us with every second position
+// compared with its window in look-back order; 210 us with these sizes (100),
+// the scan (5) and the records written at copy rate (95). 100 MB of float64
+// 104 and 87, 1 MiB 33 and 30. Bound by instruction issue: about 30 vector instructions and 2 LDS accesses per
 // 64 positions (W / 2 vector and as many scalar ones with the window
 // comparison).
 constexpr uint32_t kThreads = 256;
