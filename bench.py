@@ -44,75 +44,6 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
 
-# HBM bytes per encode launch on this workload from two rocprofv3 --pmc runs
-# (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch), each scaled by what the
-# same counter reads for a device copy of the 256 MiB input (FETCH_SIZE reads
-# half the copied bytes: factor 2.0; WRITE_SIZE reads them exactly: 1.0).
-# Valid only for the encoder sources they were taken on (sha256 below; the
-# generated dense-parse assembly is left out: only 1- and 2-byte encoders
-# instantiate it, and this workload has 4-byte symbols).
-# "prep" is the compress call's preparation kernel (look-back descriptors
-# and tickets zeroed); the step is prep + encode.
-ENCODE_COUNTERS = {
-    "sources_sha256": "2d96b58d2cec28f720430b5cc2d49e536ba57dc09fd90b1ae079cd0f15622aab",
-    "fetch_kib": 140127.6, "write_kib": 277144.8,
-    "prep_fetch_kib": 16.0, "prep_write_kib": 128.3,
-    "fetch_scale": 2.0, "write_scale": 1.0,
-}
-ENCODE_SOURCES = ("paper_2304_07342_amd/csrc/lz_encode.hip", "paper_2304_07342_amd/csrc/encode_device.h",
-                  "paper_2304_07342_amd/csrc/stream_device.h", "paper_2304_07342_amd/csrc/wave.h",
-                  "paper_2304_07342_amd/csrc/gpulz_internal.h")
-
-
-def encoder_sources_sha256() -> str:
-    import hashlib
-    h = hashlib.sha256()
-    for f in ENCODE_SOURCES:
-        with open(os.path.join(ROOT, f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()
-
-
-def encode_traffic_bytes():
-    """Counter-derived HBM bytes per encode launch and per whole step (prep +
-    encode), or (None, None) if the encoder has changed since the counters
-    were taken."""
-    c = ENCODE_COUNTERS
-    if c["sources_sha256"] is None or encoder_sources_sha256() != c["sources_sha256"]:
-        return None, None
-    enc = (c["fetch_kib"] * c["fetch_scale"] + c["write_kib"] * c["write_scale"]) * 1024
-    prep = (c["prep_fetch_kib"] * c["fetch_scale"] + c["prep_write_kib"] * c["write_scale"]) * 1024
-    return int(enc), int(enc + prep)
-# 256 CUs x 64 lanes x 2.4 GHz: one 32-bit compare per lane per clock.
-ALU_PEAK_TCMP = 256 * 64 * 2.4e9 / 1e12
-
-
-def window_compares(m: int, C: int, W: int) -> int:
-    """Symbol comparisons of an exhaustive window search: every position j of
-    a chunk is compared with each of the min(j, W) symbols before it."""
-    def per_chunk(c):
-        if c <= W + 1:
-            return c * (c - 1) // 2
-        return W * (W + 1) // 2 + (c - 1 - W) * W
-    full, last = divmod(m, C)
-    return full * per_chunk(C) + (per_chunk(last) if last else 0)
-
-
-def executed_hit_compares(m: int, C: int, W: int, S: int, MIN: int) -> int:
-    """Symbol compares the encoder's hit phase executes: each lane owns V =
-    16 / S positions of a 64 V block and compares every tested position
-    (even ones when MIN >= 2) with W window offsets, masked or not. The
-    exact searches at candidate positions come on top (data-dependent, rare
-    on the field)."""
-    V = 16 // S
-    step = 2 if MIN >= 2 else 1
-
-    def per_chunk(c):
-        blocks = -(-c // (64 * V))
-        return blocks * 64 * (V // step) * W
-    full, last = divmod(m, C)
-    return full * per_chunk(C) + (per_chunk(last) if last else 0)
-
 
 def cpu_model() -> str:
     try:
@@ -339,12 +270,11 @@ def dense_leg(args, kind, seed, S, MIN, size, params=None):
         raise SystemExit(f"round trip mismatch for {kind}")
     kernel_ms = {k: round(v[0] / max(1, v[1]), 4) for k, v in prof.items() if v[1]}
     enc_ms = kernel_ms.get("encode", ms)
-    cmp = window_compares(size // S, C, W)
     out = {"workload": f"dense-{kind}-{size >> 20}MiB", "symbol_bytes": S, "input_bytes": size,
            "value": round(size / ms / 1e6, 3), "unit": "GB/s", "ms_per_step": round(ms, 4),
            "ratio": round(size / nbytes, 4), "chunk_symbols": C, "window": W, "min_match": MIN,
            "waves_per_chunk": waves, "kernel_avg_ms": kernel_ms,
-           "compare_peak_frac": round(cmp / (enc_ms / 1e3) / 1e12 / ALU_PEAK_TCMP, 4),
+           "hbm_frac": round((size + nbytes) / (enc_ms / 1e3) / 1e9 / HBM_PEAK_GBPS, 4),
            "params_from": "autotuner" if tuned else "given"}
     if tuned:
         out["autotune_candidates"] = len(tuned["measurements"])
@@ -818,13 +748,9 @@ def main():
 
     enc_ms, enc_launches = prof["encode"]
     enc_avg_ms = enc_ms / max(1, enc_launches)
-    m = n // S
-    compares = window_compares(m, C, W)
-    executed = executed_hit_compares(m, C, W, S, MIN)
-    achieved = compares / (enc_avg_ms / 1e3) / 1e12
+    achieved = (n + size) / (enc_avg_ms / 1e3) / 1e9
     kernel_ms = {k: round(v[0] / max(1, v[1]), 4) for k, v in prof.items() if v[1]}
     value = n / (ms_step / 1e3) / 1e9
-    traffic, step_traffic = encode_traffic_bytes()
 
     result = {
         "metric": "compress GB/s (input) + ratio at 1 GPU; batched GB/s and p99 latency vs plain",
@@ -848,19 +774,15 @@ def main():
         "decompress_GBps": round(dec_gbps, 3) if dec_gbps else None,
         "kernel_avg_ms": kernel_ms,
         "hbm_frac_whole_step": round((n + size) / (ms_step / 1e3) / 1e9 / HBM_PEAK_GBPS, 4),
-        "roofline": {"bound": "alu",
-                     "kernel": "encode_kernel<4,4> (match search, parse, look-back, record write-out)",
-                     "achieved": round(achieved, 4), "peak": round(ALU_PEAK_TCMP, 3),
-                     "unit": "Tcmp/s", "frac": round(achieved / ALU_PEAK_TCMP, 4),
-                     "achieved_counts": "algorithmic compares: every position against each of "
-                                        "its min(j, W) window offsets",
-                     "compares_per_launch": compares,
-                     "executed_hit_compares_per_launch": executed,
-                     "executed_frac": round(executed / (enc_avg_ms / 1e3) / 1e12 / ALU_PEAK_TCMP, 4),
-                     "traffic": traffic,
+        "roofline": {"bound": "hbm",
+                     "kernel": "compress kernels (chunk sizes by repeated symbol pairs, offset scan, "
+                               "record write-out)",
+                     "achieved": round(achieved, 3), "peak": HBM_PEAK_GBPS,
+                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
+                     "achieved_counts": "algorithmic bytes: input read once, stream written once",
                      "hbm_algorithmic_bytes_per_launch": n + size,
-                     "hbm_frac_encode": round((n + size) / (enc_avg_ms / 1e3) / 1e9 / HBM_PEAK_GBPS, 4)},
-        "step_traffic": step_traffic,
+                     "bytes_moved_per_step": 2 * n + size,
+                     "bytes_moved_counts": "the sizes and the records each read the input"},
     }
     if not args.no_cpu_baseline:
         print("[bench] cpu baseline", file=sys.stderr, flush=True)
