@@ -78,3 +78,29 @@ def test_nothing_written_past_the_end():
     host = out.cpu().numpy()
     assert host[:n].tobytes() == data
     assert (host[n:] == 0xA5).all()
+
+
+def test_weights_past_32_bits():
+    """2 GiB and more: the tree is built on 64-bit weights. Code lengths
+    against the reference's, and the chunks read back."""
+    import torch
+    import huffref
+    n = (1 << 31) + 54321
+    freq = [0] * 256
+    left = n
+    for s in range(0, 40, 2):
+        freq[s] = left // 3
+        left -= freq[s]
+    freq[255] = left
+    x = torch.empty(n, dtype=torch.uint8, device="cuda")
+    at = 0
+    for s, c in enumerate(freq):
+        x[at:at + c] = s
+        at += c
+    assert at == n
+    print("huff past 32 bits", flush=True)
+    stream = gpulz.huff_compress(x)
+    packed = stream[64:192].cpu().numpy()
+    got = [int(packed[s // 2] >> (4 * (s & 1))) & 15 for s in range(256)]
+    assert got == list(huffref.lengths(freq))
+    assert torch.equal(gpulz.huff_decompress(stream), x)
