@@ -149,9 +149,14 @@ struct BuildLds {
 // by one were up to 255 LDS round trips (build_kernel on the LZSS stream of
 // 1 MiB or 128 MiB of codes: 64 us with one join at a time and the ranks
 // counted in a loop, 34 us so; what is left is the chain of rounds on one
-// wave). W is uint32_t when the weights sum
-// below 2^31 (cheaper compares; below 2^31 so that no weight equals the
+// wave). A round costs about six single joins, so few symbols are joined one
+// by one (47 symbols of raw uint16 codes, built five times for the length
+// limit: 1 MiB 150 us in rounds, 103 one by one), and weights that grow
+// like a chain, whose rounds are a join or two: after such a round the next 8
+// joins are made one by one, then 16 and so on. W is uint32_t when the weights
+// sum below 2^31 (cheaper compares; below 2^31 so that no weight equals the
 // 32-bit infinity), else uint64_t. Returns the number of internal nodes.
+constexpr uint32_t kSingleJoins = 96;
 template <typename W>
 __device__ uint32_t merge(BuildLds& sm, uint32_t m, uint32_t lane) {
   const W kInf = (W)~0ull;
@@ -162,18 +167,62 @@ __device__ uint32_t merge(BuildLds& sm, uint32_t m, uint32_t lane) {
     leaf[q] = x < m ? (W)(sm.key[x] >> 8) : kInf;
   }
   uint32_t li = 0, kf = 0, kc = 0;  // first leaf and node at hand, nodes made
+  uint32_t single = m <= kSingleJoins ? m : 0u, next_single = 8;  // joins to make one by one
   while (kc + 1 < m) {
-    W node[4];
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      const uint32_t x = 64 * q + lane;
-      node[q] = x < kc ? (W)sm.iw[x] : kInf;
+    if (single) {
+      // one lane joins the two lightest nodes, `single` times
+      if (lane == 0) {
+        for (; single && kc + 1 < m; --single) {
+          const W l0 = li < m ? (W)(sm.key[li] >> 8) : kInf;
+          const W l1 = li + 1 < m ? (W)(sm.key[li + 1] >> 8) : kInf;
+          const W i0 = kf < kc ? (W)sm.iw[kf] : kInf;
+          const W i1 = kf + 1 < kc ? (W)sm.iw[kf + 1] : kInf;
+          uint32_t na, nb;
+          W w;
+          if (l0 <= i0) {
+            na = li++;
+            w = l0;
+            if (l1 <= i0) {
+              nb = li++;
+              w += l1;
+            } else {
+              nb = 256 + kf++;
+              w += i0;
+            }
+          } else {
+            na = 256 + kf++;
+            w = i0;
+            if (l0 <= i1) {
+              nb = li++;
+              w += l0;
+            } else {
+              nb = 256 + kf++;
+              w += i1;
+            }
+          }
+          sm.iw[kc] = w;
+          sm.parent[na] = sm.parent[nb] = (uint16_t)(256 + kc);
+          ++kc;
+        }
+      }
+      single = 0;
+      li = uniform(li);
+      kf = uniform(kf);
+      kc = uniform(kc);
+      wave_sync();
+      continue;
     }
     const W l0 = li < m ? (W)(sm.key[li] >> 8) : kInf;
     const W l1 = li + 1 < m ? (W)(sm.key[li + 1] >> 8) : kInf;
     const W i0 = kf < kc ? (W)sm.iw[kf] : kInf;
     const W i1 = kf + 1 < kc ? (W)sm.iw[kf + 1] : kInf;
     const W t = l0 <= i0 ? l0 + (l1 <= i0 ? l1 : i0) : i0 + (l0 <= i1 ? l0 : i1);
+    W node[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t x = 64 * q + lane;
+      node[q] = x < kc ? (W)sm.iw[x] : kInf;
+    }
     uint32_t le = 0, ie = 0;
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q) {
@@ -237,6 +286,12 @@ __device__ uint32_t merge(BuildLds& sm, uint32_t m, uint32_t lane) {
     li = le - (k & 1u && !waits_node ? 1u : 0u);
     kf = ie - (waits_node ? 1u : 0u);
     kc += pairs;
+    if (pairs <= 2) {
+      single = next_single;
+      next_single *= 2;
+    } else {
+      next_single = 8;
+    }
   }
   return kc;
 }
