@@ -112,8 +112,8 @@ gpulz_status gpulz_compress_workspace_size(uint64_t nbytes, uint32_t symbol_byte
  * 1024 chunks) and a kernel that writes the table and the records. Inputs of
  * more than 2^27 chunks give GPULZ_ERR_UNSUPPORTED.
  * waves_per_chunk of the width's defaults (gpulz_default_params) is used by
- * the general encoder only (min_match 1, larger minimum matches of narrow
- * symbols, larger chunks); it changes speed, never the bytes.
+ * the general encoder only (min_match 1, larger chunks); it changes speed,
+ * never the bytes.
  * Asynchronous on `stream` (0 = null stream). Same bytes as any other
  * conforming producer for the same input and parameters. Calls that overlap
  * must use distinct workspaces. */
@@ -249,7 +249,7 @@ gpulz_status gpulz_decompress_noalloc(const void* d_in, uint64_t in_bytes, void*
 /* Parameters for one symbol width; zero fields take the library default for
  * that width. waves_per_chunk is the workgroup size of the general chunk
  * encoder in wavefronts (1, 2 or 4); one batch launch uses the largest value
- * given. The encoders that parameters with min_match = 2 usually take have
+ * given. The encoders that parameters with min_match >= 2 usually take have
  * workgroup sizes of their own. */
 typedef struct {
   uint32_t chunk_symbols;

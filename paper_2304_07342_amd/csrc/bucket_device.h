@@ -103,14 +103,11 @@ __host__ __device__ constexpr uint64_t chunk_lds(uint32_t C, uint32_t W, uint32_
 // Window columns of that split parse for a window of wc columns: one variant
 // for bytes, two for 2-byte symbols (one or two streaming columns).
 template <int S, int WC> constexpr int kFallbackWC = S == 2 && WC <= 2 ? 2 : 4;
-// Whether this encoder takes chunks of C symbols with these parameters: MIN = 2,
-// and larger MIN where the split parse would be the other choice (`few`).
-// MIN = 1 needs single symbols as candidates; one-wave encoders with larger MIN
-// keep their own parse. C: the parse has a segment of at most 32 positions for
-// each of 256 threads.
-__host__ constexpr bool takes(uint32_t C, uint32_t MIN, uint64_t lds, bool few) {
-  return (MIN == 2 || (MIN > 2 && few && C <= kSpecMaxSyms)) && C <= kMaxSyms &&
-         lds <= kMaxGroupLdsBytes;
+// Whether this encoder takes chunks of C symbols with these parameters. MIN = 1
+// needs single symbols as candidates. C: the parse has a segment of at most 32
+// positions for each of 256 threads.
+__host__ constexpr bool takes(uint32_t C, uint32_t MIN, uint64_t lds) {
+  return MIN >= 2 && C <= kMaxSyms && lds <= kMaxGroupLdsBytes;
 }
 
 __device__ __forceinline__ uint32_t hash2(uint32_t x) {

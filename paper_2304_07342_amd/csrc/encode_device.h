@@ -1479,7 +1479,7 @@ __device__ __forceinline__ Parsed parse_chunk(const ChunkJob& job, const uint8_t
   uint32_t ntok = 0, pay = 0, desc = 0, g0 = kNoGroup;
   uint32_t p = 0;
   if constexpr (kStreamSearch<S>) {
-    if (dense && job.MIN <= 2) {
+    if (dense) {
       const uint32_t rest = parse_dense<S, WC>(stage, 0, c, c, job.W, job.MIN, wmask, lane,
                                                desc, [&](uint32_t d64) {
         emit_group<S, kSinglePass>(64, d64, ntok >> 6, win, slot, job.flag_area, pay, g0);
@@ -1575,12 +1575,13 @@ __device__ void encode_chunk(const ChunkJob& job, uint8_t* lds) {
   // accordingly (candidates are a superset of pointer starts, and every
   // candidate still gets the exact search).
   //
-  // Dense chunks (streaming search, one wave per chunk): the streaming
-  // search compares every position it passes anyway, at a fixed cost per
-  // position, while the per-candidate search costs several times that, so
-  // the bitmap only pays where candidates are rare. If at least 1/4 of the
-  // tested positions of the first block are hits, the rest of the bitmap is
-  // not built and every position is a candidate.
+  // Dense chunks (streaming parse: one wave per chunk, MIN <= 2): the
+  // streaming search compares every position it passes anyway, at a fixed
+  // cost per position, while the per-candidate search costs several times
+  // that, so the bitmap only pays where candidates are rare. If at least 1/4
+  // of the tested positions of the first block are hits, the rest of the
+  // bitmap is not built and every position is a candidate. At larger MIN the
+  // parse goes by the bitmap, which has to be whole.
   const bool sampled = job.MIN >= 2;
   bool dense = false;
   {
@@ -1588,7 +1589,7 @@ __device__ void encode_chunk(const ChunkJob& job, uint8_t* lds) {
     const uint32_t nblocks = (c + kBlock - 1) / kBlock;
     uint32_t b0 = wave;
     if constexpr (kStreamSearch<S>) {
-      if (nwaves == 1 && nblocks > 1) {
+      if (nwaves == 1 && nblocks > 1 && job.MIN <= 2) {
         if (sampled) hit_block<S, true, 2>(w4, 0, job.W, hits);
         else hit_block<S, true, 1>(w4, 0, job.W, hits);
         wave_sync();

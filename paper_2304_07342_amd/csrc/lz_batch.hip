@@ -393,7 +393,7 @@ hipError_t launch_width_wc(const BatchEncArgs& a, hipStream_t s) {
   if constexpr (S <= 2) {
     constexpr int WF = enc::bucket::kFallbackWC<S, WC>;
     const size_t lds = enc::bucket::chunk_lds<S, WF>(C, a.wp.W[WI], 256);
-    if (enc::bucket::takes(C, a.wp.MIN[WI], lds, false))
+    if (enc::bucket::takes(C, a.wp.MIN[WI], lds))
       return launch_persistent<S, WI, WF, BatchEncoder::kBucket>(a, 256, lds, s);
   }
   if constexpr (S >= 4) {

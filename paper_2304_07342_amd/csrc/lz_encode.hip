@@ -283,7 +283,7 @@ hipError_t launch_sw(const FusedArgs& a, uint32_t waves, hipStream_t s) {
     constexpr uint32_t kNT = 256;
     const uint32_t threads = a.N <= kBucketFewChunks ? 1024 : kNT;
     const size_t lds = enc::bucket::chunk_lds<S, WF>(a.C, a.W, threads);
-    if (enc::bucket::takes(a.C, a.MIN, lds, a.N <= kSpecMaxChunksNarrow)) {
+    if (enc::bucket::takes(a.C, a.MIN, lds)) {
       const dim3 grid((uint32_t)a.nchunks), block(threads);
       if (threads == 1024)
         hipLaunchKernelGGL((encode_bucket_kernel<S, WF, 1024>), grid, block, lds, s, a);
