@@ -8,15 +8,8 @@
 //            chunks (one u64 per group; the sum must end exactly at the
 //            stream's end); a chunk's record offset is its group's offset
 //            plus a 64-lane prefix sum over the group's table entries;
-//   chunk    (1- and 2-byte symbols, many chunks) one wavefront per chunk walks the tokens 64
-//            at a time: lane l takes token t + l, its flag bit gives its kind,
-//            mbcnt over the literal / pointer ballots its payload offset, a
-//            wave scan of the token lengths its output position. Literals are
-//            written into an LDS ring of recent symbols; then the new symbols
-//            are taken 64 at a time, one per lane: a pointer's symbol follows
-//            its source back to a literal or out of the 64, in registers, and
-//            copies it. Finished symbols stream out to HBM; the next tokens'
-//            payload is loaded meanwhile;
+//   chunk    (all literals: F and P say so and the flag bytes are zero) copied
+//            from the stream to the output;
 //   chunk    (4- and 8-byte symbols, or few chunks; at most 4096 symbols and
 //            16 KiB) one workgroup of 256 threads per chunk: the record is staged into
 //            LDS with 16-byte loads; block-wide scans over the flag bits and
@@ -26,16 +19,17 @@
 //            pointers in token order (a run of pointers whose sources are
 //            already final is copied together), and the chunk is written to
 //            HBM with 16-byte stores;
-//   chunk    (any other chunk) one wavefront walks the tokens 64 at a time: lane l
-//            takes token t + l, its flag bit gives its kind, mbcnt over the
-//            literal / pointer ballots gives its payload offset, a wave scan
-//            of the token lengths gives its output position. Literals are
-//            written into an LDS ring of recent symbols; pointers are then
-//            resolved in token order, each copied by all 64 lanes (a pointer
-//            never overlaps itself because its length never exceeds its
-//            offset). Finished symbols stream out to HBM. The ring keeps the
-//            last 256 symbols (the largest offset), so LDS use does not
-//            depend on the chunk size.
+//   chunk    (1- and 2-byte symbols in many chunks, and longer chunks) one
+//            wavefront walks the tokens 64 at a time: lane l takes token t + l,
+//            its flag bit gives its kind,
+//            mbcnt over the literal / pointer ballots its payload offset, a
+//            wave scan of the token lengths its output position. Literals are
+//            written into an LDS ring of recent symbols; then the new symbols
+//            are taken 64 at a time, one per lane: a pointer's symbol follows
+//            its source back to a literal or out of the 64, in registers, and
+//            copies it. Finished symbols stream out to HBM; the next tokens'
+//            payload is loaded meanwhile. The ring keeps the last 256 symbols
+//            (the largest offset), so LDS use does not depend on the chunk size.
 // Every rule the encoder guarantees is checked; a broken one makes the
 // stream GPULZ_ERR_CORRUPT.
 #pragma once
@@ -72,7 +66,7 @@ __device__ inline void parse_header(const uint8_t* h, uint64_t in_bytes, DecodeP
     p.n = (uint64_t)w[5] << 32 | w[4];
     p.N = (uint64_t)w[7] << 32 | w[6];
     const uint64_t total = (uint64_t)w[9] << 32 | w[8];
-    p.r = w[10] & 0xFFu;
+    p.r = (uint16_t)(w[10] & 0xFFu);
     ok = ok && (p.S == 1 || p.S == 2 || p.S == 4 || p.S == 8) && p.C >= 1 && p.C <= (1u << 24) &&
          p.W >= 1 && p.W <= kMaxWindow && p.MIN >= 1;
     if (ok) {
@@ -151,68 +145,7 @@ __device__ inline uint64_t record_offset(const uint8_t* in, const uint64_t* grou
   return group_off[g] + __shfl(s, 63, 64);
 }
 
-// Decode one chunk (wave-wide); returns false if the chunk breaks a rule.
-template <int S>
-__device__ bool decode_chunk(const uint8_t* flags, uint32_t F, uint32_t P, uint32_t c, uint32_t W,
-                             uint32_t MIN, typename SymType<S>::T* out, uint8_t* ring_raw) {
-  using T = typename SymType<S>::T;
-  constexpr uint32_t R = kDecodeRingBytes / S;    // ring capacity in symbols
-  constexpr uint32_t SPAN = R - 2 * kMaxWindow;   // new symbols per step
-  T* ring = reinterpret_cast<T*>(ring_raw);
-  const uint8_t* pay = flags + F;
-  const uint32_t lane = lane_id();
-  uint32_t q = 0, u = 0;
-  uint64_t t = 0;
-  while (q < c) {
-    const uint64_t tok = t + lane;
-    const bool has = tok < 8ull * F;
-    const bool ptr = has && ((flags[tok >> 3] >> (tok & 7)) & 1u);
-    const uint64_t pm = ballot(ptr);
-    const uint64_t lm = ballot(has && !ptr);
-    const uint32_t off = u + S * mbcnt(lm) + 2u * mbcnt(pm);
-    bool ok = has && off + (ptr ? 2u : (uint32_t)S) <= P;
-    uint32_t L = 1, O = 1;
-    if (ptr && ok) {
-      L = pay[off];
-      O = pay[off + 1] ? pay[off + 1] : 256u;
-    }
-    const uint32_t len = has ? L : 0;
-    const uint32_t pos = q + wave_incl_scan(len) - len;
-    const uint32_t lim = min(c, q + SPAN);
-    const bool take = has && pos < lim;
-    const uint64_t tm = ballot(take);
-    if (tm == 0) return false;  // flags exhausted before the chunk is complete
-    if (ptr) ok = ok && L >= MIN && O <= W && O <= pos && L <= O && pos + L <= c;
-    if (ballot(take && !ok)) return false;
-    if (take && !ptr) {
-      uint64_t v = 0;
-#pragma unroll
-      for (int b = 0; b < S; ++b) v |= (uint64_t)pay[off + b] << (8 * b);
-      ring[pos & (R - 1)] = (T)v;
-    }
-    wave_sync();
-    uint64_t mt = pm & tm;
-    while (mt) {
-      const uint32_t j = (uint32_t)__ffsll((unsigned long long)mt) - 1;
-      mt &= mt - 1;
-      const uint32_t pj = readlane(pos, j), Lj = readlane(L, j), Oj = readlane(O, j);
-      for (uint32_t k = lane; k < Lj; k += 64) ring[(pj + k) & (R - 1)] = ring[(pj - Oj + k) & (R - 1)];
-      wave_sync();
-    }
-    const uint32_t last = 63u - (uint32_t)__clzll(tm);
-    const uint32_t nq = readlane(pos + len, last);
-    for (uint32_t k = q + lane; k < nq; k += 64) out[k] = ring[k & (R - 1)];
-    wave_sync();
-    t += popc64(tm);
-    u += S * popc64(lm & tm) + 2u * popc64(pm & tm);
-    q = nq;
-  }
-  if ((t + 7) / 8 != F || u != P) return false;
-  if (t < 8ull * F && (flags[F - 1] >> (uint32_t)(t - 8ull * (F - 1))) != 0) return false;
-  return true;
-}
-
-// ---- wave decoder of 1- and 2-byte symbols ---------------------------------
+// ---- wave decoder -----------------------------------------------------------
 
 constexpr uint32_t kRingSyms = 1024;  // symbols of a wave's ring
 constexpr uint32_t kFlushSyms = 256;  // symbols written out at once
@@ -221,6 +154,7 @@ constexpr uint32_t kFlushSyms = 256;  // symbols written out at once
 // new ones fit the ring.
 constexpr uint32_t kSpanSyms = kRingSyms - kFlushSyms - kMaxMatch - 1;
 constexpr uint32_t kStepSyms = kSpanSyms + 256;  // symbols of a step, at most
+constexpr uint32_t kFewPointers = 8;  // a lone wave copies so many one by one
 constexpr uint32_t kShortFill = 8;  // longer pointers' offsets are laid out by all lanes
 template <int S> struct WaveLds {
   typename SymType<S>::T ring[kRingSyms];
@@ -240,15 +174,18 @@ __device__ __forceinline__ uint64_t load_bytes8(const uint8_t* p, uint32_t k, ui
 
 // Decode one chunk of c symbols with one wavefront; returns false (uniformly)
 // if it breaks a rule. `flags` is the record (F flag bytes, then P payload
-// bytes; no byte past them is read).
-template <int S>
+// bytes; no byte past them is read). kAlone: the wave is one of few on its compute
+// unit, so the chain of a round's steps counts: a round of few pointers copies
+// them one after the other (with all wave slots taken that form costs more than
+// it saves).
+template <int S, bool kAlone>
 __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, uint32_t c,
-                                  uint32_t W, uint32_t MIN, typename SymType<S>::T* out,
-                                  WaveLds<S>& lds) {
+                                  uint32_t W, uint32_t MIN, uint8_t* dst, uint8_t* lds_bytes) {
   using T = typename SymType<S>::T;
-  using Quad = typename SymType<4 * S>::T;
+  using V = typename SymType<S == 8 ? 8 : 4>::T;  // holds a token's payload
+  WaveLds<S>& lds = *reinterpret_cast<WaveLds<S>*>(lds_bytes);
+  T* const out = reinterpret_cast<T*>(dst);
   T* const ring = lds.ring;
-  static_assert(S <= 2, "a token's payload is at most two bytes");
   constexpr uint32_t M = kRingSyms - 1;
   const uint32_t lane = lane_id();
   if (F > (c + 7) / 8) return false;  // more tokens than symbols
@@ -260,10 +197,13 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
   uint32_t t = 0, u = 0;  // tokens taken, their payload bytes
   uint64_t fw = 0;       // flag words of 64 rounds, one per lane
 
-  // this lane's payload (2 bytes, or 1 at the payload's end) at offset `off`
-  auto payload = [&](bool has, uint32_t off) -> uint32_t {
-    uint32_t v = 0;
-    if (has && off + 2 <= P) {
+  // this lane's payload at offset `off` (0 if it does not end in the payload):
+  // 2 bytes of a pointer, S of a literal, in the lower bits
+  auto payload = [&](bool has, bool ptr, uint32_t off) -> V {
+    V v = 0;
+    if (S >= 4 && has && !ptr) {
+      if (off + S <= P) __builtin_memcpy(&v, pay + off, S);
+    } else if (has && off + 2 <= P) {
       uint16_t x;
       __builtin_memcpy(&x, pay + off, 2);
       v = x;
@@ -273,7 +213,8 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
     return v;
   };
   auto flush = [&](uint32_t n) {  // writes out symbols [done, done + n)
-    if (wide && n == kFlushSyms) {  // four symbols per lane
+    if (S <= 2 && wide && n == kFlushSyms) {  // four symbols per lane
+      using Quad = typename SymType<S <= 2 ? 4 * S : S>::T;
       reinterpret_cast<Quad*>(out + done)[lane] = reinterpret_cast<const Quad*>(ring + (done & M))[lane];
     } else {
       for (uint32_t k = lane; k < n; k += 64) out[done + k] = ring[(done + k) & M];
@@ -282,10 +223,12 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
   };
 
   uint64_t pm_next = 0;
-  uint32_t v_next = 0, off_next = 0, u_next = 0;
+  V v_next = 0;
+  uint32_t off_next = 0, u_next = 0;
   for (uint32_t r = 0; r <= rounds; ++r) {
     const uint64_t pm = pm_next;
-    const uint32_t v = v_next, off = off_next;
+    const V v = v_next;
+    const uint32_t off = off_next;
     const uint32_t base = 64 * (r - 1);  // this round's first token (r >= 1)
     if (r < rounds) {  // the next round's flags and payload
       if ((r & 63u) == 0) fw = 8 * (r + lane) < F ? load_bytes8(flags, r + lane, F) : 0ull;
@@ -295,7 +238,7 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
       const uint64_t hm = left >= 64 ? ~0ull : (1ull << left) - 1ull;
       const uint64_t lm = hm & ~pm_next;
       off_next = u_next + S * mbcnt(lm) + 2u * mbcnt(pm_next);
-      v_next = payload(hm >> lane & 1, off_next);
+      v_next = payload(hm >> lane & 1, pm_next >> lane & 1, off_next);
       u_next += S * popc64(lm) + 2u * popc64(pm_next);
     }
     if (r == 0) continue;
@@ -304,8 +247,8 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
     const bool has = lane < left;
     const bool ptr = pm >> lane & 1;
     const uint32_t sz = ptr ? 2u : (uint32_t)S;
-    const uint32_t L = ptr ? v & 0xFFu : 1u;
-    const uint32_t O = ptr ? ((v >> 8) - 1u & 0xFFu) + 1u : 1u;
+    const uint32_t L = ptr ? (uint32_t)v & 0xFFu : 1u;
+    const uint32_t O = ptr ? (((uint32_t)v >> 8) - 1u & 0xFFu) + 1u : 1u;
     const uint32_t len = has ? L : 0u;
     const uint32_t incl = wave_incl_scan(len);
     const uint32_t pos = q + incl - len;
@@ -315,9 +258,24 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
     if (ptr) bad = bad || L < MIN || O > W || O > pos || L > O || pos + L > c;
     if (ballot((tm >> lane & 1) && bad)) return false;
     if (tm == 0) break;  // the chunk was complete before this round
-    // usually one step; a round of long pointers takes several
     uint64_t todo = tm;
-    for (;;) {
+    if (kAlone && total <= kSpanSyms && popc64(tm & pm) <= kFewPointers) {
+      if ((tm & ~pm) >> lane & 1) ring[pos & M] = (T)v;
+      for (uint64_t m = tm & pm; m; m &= m - 1) {
+        const uint32_t j = (uint32_t)__builtin_ctzll(m);
+        const uint32_t pj = readlane(pos, j), Lj = readlane(L, j), Oj = readlane(O, j);
+        wave_sync();
+        for (uint32_t k = lane; k < Lj; k += 64) ring[(pj + k) & M] = ring[(pj - Oj + k) & M];
+      }
+      q = tm & pm ? readlane(pos + len, 63u - (uint32_t)__builtin_clzll(tm)) : q + popc64(tm);
+      todo = 0;
+      if (q - done >= kFlushSyms) {
+        wave_sync();
+        while (q - done >= kFlushSyms) flush(kFlushSyms);
+      }
+    }
+    // usually one step; a round of long pointers takes several
+    while (todo) {
       uint64_t now = todo;
       if (total > kSpanSyms) now = ballot((todo >> lane & 1) && pos < q + kSpanSyms);
       const bool mine = now >> lane & 1;
@@ -357,7 +315,6 @@ __device__ bool decode_chunk_wave(const uint8_t* flags, uint32_t F, uint32_t P, 
       todo &= ~now;
       q += n;
       while (q - done >= kFlushSyms) flush(kFlushSyms);
-      if (!todo) break;
     }
     t += popc64(tm);
     u += S * popc64(tm & ~pm) + 2u * popc64(tm & pm);
@@ -794,22 +751,60 @@ __device__ inline ChunkPlace chunk_place(const uint8_t* in, const DecodeParams& 
 // LDS of one wave of decode_stream_chunk_wave.
 constexpr uint32_t kWaveLds = (sizeof(WaveLds<2>) + 15) / 16 * 16;
 
-// Decode chunk i of a validated stream of 1- or 2-byte symbols with one
-// wavefront and kWaveLds bytes of LDS; false (uniformly) if it is corrupt.
-__device__ inline bool decode_stream_chunk_wave(const uint8_t* in, const DecodeParams& p,
-                                                const uint64_t* group_off, uint64_t i,
-                                                uint8_t* out, uint8_t* lds) {
+// Decode chunk i of a validated stream (of in_bytes bytes) of 1- or 2-byte
+// symbols with one wavefront and kWaveLds bytes of LDS; false (uniformly) if it
+// is corrupt. A record of literals alone is the chunk itself behind its zero
+// flag bytes and is copied (64 MiB of random uint16, C 2048: 49 us; token by
+// token 120).
+__device__ inline bool decode_stream_chunk_wave(const uint8_t* in, uint64_t in_bytes,
+                                                const DecodeParams& p, const uint64_t* group_off,
+                                                uint64_t i, uint8_t* out, uint8_t* lds) {
   const ChunkPlace k = chunk_place(in, p, group_off, i, out);
   const uint32_t F = k.F, P = k.P, c = k.c;
-  if (p.S == 1)
-    return decode_chunk_wave<1>(k.rec, F, P, c, p.W, p.MIN, k.dst, *reinterpret_cast<WaveLds<1>*>(lds));
-  return decode_chunk_wave<2>(k.rec, F, P, c, p.W, p.MIN, reinterpret_cast<uint16_t*>(k.dst),
-                              *reinterpret_cast<WaveLds<2>*>(lds));
+  if (F == (c + 7) / 8 && P == c * p.S) {
+    const uint32_t lane = lane_id();
+    uint64_t set = 0;
+    for (uint32_t w = lane; 8 * w < F; w += 64) set |= load_bytes8(k.rec, w, F);
+    if (!ballot(set != 0)) {
+      stream::copy_unaligned<2>(k.dst, k.rec + F, P, in + in_bytes, lane, 64);
+      return true;
+    }
+  }
+  if (p.S == 1) return decode_chunk_wave<1, false>(k.rec, F, P, c, p.W, p.MIN, k.dst, lds);
+  return decode_chunk_wave<2, false>(k.rec, F, P, c, p.W, p.MIN, k.dst, lds);
+}
+
+// Whether the chunks of a validated stream are decoded by one wave each, where
+// `chunks` chunks of 1- and 2-byte symbols are decoded together. A wave takes
+// half the instructions of a workgroup but about 1 us per 64 tokens, so it needs
+// many chunks, and the more the longer they are. Workgroup against wave, in us:
+// Zipf bytes, C 4096: 1600 chunks 64 and 70, 2048 chunks 70 and 69, 4096 chunks
+// 130 and 83; uint16 codes, C 4096: 1600 chunks 64 and 63; C 2048: 42 and 37.
+// Where pointers save next to nothing a chunk is nearly all literals, which
+// workgroups decode sooner: random bytes, C 4096: 3072 chunks 54 and 81, 8192
+// chunks 130 and 125; C 2048: 3072 chunks 40 and 46, 4096 chunks 50 and 47. At 2
+// bytes a symbol that can be told from single pointers: with less than one in
+// 1024 symbols most chunks are copied, and the others want to end soon (64 MiB
+// of random uint16 with one pointer, C 4096: 41 and 57). Chunks too long for
+// the workgroup decoder are one wave's work in either kernel; the wave kernel has
+// room for more of them at a time.
+constexpr uint32_t kFewestForWaves = 1024;
+__device__ __forceinline__ bool takes_waves(const DecodeParams& p, uint64_t in_bytes,
+                                            uint64_t chunks) {
+  if (p.S > 2) return false;
+  if (p.C > kFastSyms) return chunks > kFewestForWaves;
+  const uint64_t literals = p.m * p.S + p.m / 8 + p.N;  // record bytes without a pointer
+  const uint64_t records = in_bytes - kHeaderBytes - 8 * p.N;
+  const uint64_t saved = literals > records ? literals - records : 0;
+  if (p.S == 2 && saved < p.m / 1024) return false;
+  return chunks > (saved < p.m / 32 ? max(kFewestForWaves, 7 * p.C / 4) : 1280 + p.C / 8);
 }
 
 // Decode chunk i of a validated stream of in_bytes bytes with the whole
 // workgroup; false (uniformly) if it is corrupt. Chunks the workgroup
-// decoder does not take go to the wave decoder on wave 0.
+// decoder does not take go to the wave decoder on wave 0 (1.5 MB of uint16
+// codes, C 8192: 97 us; 268 with the pointers of 64 tokens copied one by one;
+// 1 MiB of uint32 out of 16 values: 114 and 409).
 __device__ inline bool decode_stream_chunk_block(const uint8_t* in, uint64_t in_bytes,
                                                  const DecodeParams& p, const uint64_t* group_off,
                                                  uint64_t i, uint8_t* out, BlockLds& sm) {
@@ -833,10 +828,10 @@ __device__ inline bool decode_stream_chunk_block(const uint8_t* in, uint64_t in_
   if (wave == 0) {
     bool ok;
     switch (p.S) {
-      case 1: ok = decode_chunk<1>(rec, F, P, c, p.W, p.MIN, reinterpret_cast<uint8_t*>(dst), sm.out); break;
-      case 2: ok = decode_chunk<2>(rec, F, P, c, p.W, p.MIN, reinterpret_cast<uint16_t*>(dst), sm.out); break;
-      case 4: ok = decode_chunk<4>(rec, F, P, c, p.W, p.MIN, reinterpret_cast<uint32_t*>(dst), sm.out); break;
-      default: ok = decode_chunk<8>(rec, F, P, c, p.W, p.MIN, reinterpret_cast<uint64_t*>(dst), sm.out); break;
+      case 1: ok = decode_chunk_wave<1, true>(rec, F, P, c, p.W, p.MIN, dst, sm.out); break;
+      case 2: ok = decode_chunk_wave<2, true>(rec, F, P, c, p.W, p.MIN, dst, sm.out); break;
+      case 4: ok = decode_chunk_wave<4, true>(rec, F, P, c, p.W, p.MIN, dst, sm.out); break;
+      default: ok = decode_chunk_wave<8, true>(rec, F, P, c, p.W, p.MIN, dst, sm.out); break;
     }
     if (lane_id() == 0) sm.scratch[15] = ok;
   }

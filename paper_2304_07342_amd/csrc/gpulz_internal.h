@@ -110,7 +110,9 @@ size_t encode_scan_lds_bytes(uint32_t C, uint32_t S);
 
 struct DecodeParams {
   int32_t status;
-  uint32_t S, C, W, MIN, r;
+  uint32_t S, C, W, MIN;
+  uint16_t r;
+  uint16_t waves;  // one wave per chunk decodes it (else one workgroup)
   uint64_t n, m, N;
 };
 

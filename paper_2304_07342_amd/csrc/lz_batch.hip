@@ -354,8 +354,8 @@ __global__ __launch_bounds__(kWaveThreads, 8) void batch_decode_wave_kernel(Batc
     const BatchDecBuf& e = a.bufs[b];
     if (e.p.status != kOk || e.p.S > 2) continue;
     const bool ok = dec::decode_stream_chunk_wave(
-        static_cast<const uint8_t*>(a.in_ptrs[b]), e.p, a.group_off + e.group_base, g - e.chunk_base,
-        static_cast<uint8_t*>(a.out_ptrs[b]), lds + wave * dec::kWaveLds);
+        static_cast<const uint8_t*>(a.in_ptrs[b]), a.in_bytes[b], e.p, a.group_off + e.group_base,
+        g - e.chunk_base, static_cast<uint8_t*>(a.out_ptrs[b]), lds + wave * dec::kWaveLds);
     if (!ok && lane_id() == 0) atomicExch(&a.status[b], kCorrupt);
   }
 }

@@ -14,18 +14,8 @@ namespace gpulz {
 namespace {
 
 constexpr uint32_t kPrepThreads = 1024;
-// Streams of 1- and 2-byte symbols with more chunks than this are decoded by
-// one wave per chunk, which takes half the instructions but about 2 us per 64
-// tokens; below it the whole workgroup takes each chunk. Zipf bytes (C 4096),
-// wave against workgroup: 1024 chunks 62 and 36 us, 2048 chunks 66 and 64 us,
-// 4096 chunks 81 and 119 us; uint16 codes (C 2048): 36 and 28, 39 and 46, 46
-// and 82 us.
-constexpr uint64_t kFewChunks = 1536;
 constexpr uint32_t kWaveThreads = 1024;
 constexpr uint32_t kWaveBlocks = 256 * 2;  // 32 waves per CU
-__device__ __forceinline__ bool by_waves(const DecodeParams& p) {
-  return p.S <= 2 && p.N > kFewChunks;
-}
 constexpr uint32_t kDecodeBlocks = 256 * 4;  // 4 workgroups of ~33 KiB LDS per CU
 
 __global__ __launch_bounds__(kPrepThreads) void decode_prepare_kernel(DecodePrepArgs a) {
@@ -49,6 +39,7 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prepare_kernel(DecodePrep
       *a.out_bytes = 0;
     } else {
       p.status = a.capacity < p.n ? kOutOfSpace : kOk;
+      p.waves = dec::takes_waves(p, a.in_bytes, p.N);
       *a.out_bytes = p.n;
     }
     *a.params = p;
@@ -59,7 +50,7 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prepare_kernel(DecodePrep
 __global__ __launch_bounds__(dec::kDecThreads, 4) void decode_kernel(DecodeArgs a) {
   __shared__ __align__(16) dec::BlockLds sm;
   const DecodeParams p = *a.params;
-  if (p.status != kOk || by_waves(p)) return;
+  if (p.status != kOk || p.waves) return;
   if (blockIdx.x == 0 && threadIdx.x < p.r) a.out[p.m * p.S + threadIdx.x] = a.in[48 + threadIdx.x];
   for (uint64_t i = blockIdx.x; i < p.N; i += gridDim.x) {
     const bool ok = dec::decode_stream_chunk_block(a.in, a.in_bytes, p, a.group_off, i, a.out, sm);
@@ -70,12 +61,12 @@ __global__ __launch_bounds__(dec::kDecThreads, 4) void decode_kernel(DecodeArgs 
 __global__ __launch_bounds__(kWaveThreads, 8) void decode_wave_kernel(DecodeArgs a) {
   __shared__ __align__(16) uint8_t lds[kWaveThreads / 64 * dec::kWaveLds];
   const DecodeParams p = *a.params;
-  if (p.status != kOk || !by_waves(p)) return;
+  if (p.status != kOk || !p.waves) return;
   if (blockIdx.x == 0 && threadIdx.x < p.r) a.out[p.m * p.S + threadIdx.x] = a.in[48 + threadIdx.x];
   const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint64_t waves = (uint64_t)gridDim.x * (kWaveThreads / 64);
   for (uint64_t i = blockIdx.x + (uint64_t)wave * gridDim.x; i < p.N; i += waves) {
-    const bool ok = dec::decode_stream_chunk_wave(a.in, p, a.group_off, i, a.out,
+    const bool ok = dec::decode_stream_chunk_wave(a.in, a.in_bytes, p, a.group_off, i, a.out,
                                                   lds + wave * dec::kWaveLds);
     if (!ok && lane_id() == 0) atomicExch(a.status, kCorrupt);
   }
@@ -143,8 +134,8 @@ hipError_t launch_decode_chunks(const DecodeArgs& a, hipStream_t s) {
   // a chunk takes at least 10 stream bytes (table entry, a flag byte and a
   // payload byte): small streams cannot have the many chunks of the wave
   // decoder, or not enough for all its workgroups
-  const uint64_t most = a.in_bytes > kHeaderBytes ? (a.in_bytes - kHeaderBytes) / 10 : 0;
-  if (most <= kFewChunks) return hipSuccess;
+  const uint64_t most = decode_max_chunks(a.in_bytes);
+  if (most <= dec::kFewestForWaves) return hipSuccess;
   constexpr uint32_t kPer = kWaveThreads / 64;
   const uint64_t blocks = (most + kPer - 1) / kPer;
   hipLaunchKernelGGL(decode_wave_kernel, dim3((uint32_t)(blocks < kWaveBlocks ? blocks : kWaveBlocks)),

@@ -103,7 +103,8 @@ __device__ __forceinline__ uint4 load_group(const uint32_t* q, uint32_t sh, cons
 // Copies len bytes between any two addresses of global memory: bytes up to the
 // first 16-byte aligned destination word, aligned 16-byte words (each from
 // dword-aligned reads, funnel-shifted by the same offset), the last bytes. No
-// dword that reaches src_end is read. Four words per thread in flight.
+// dword that reaches src_end is read. kFlight words per thread in flight.
+template <uint32_t kFlight = 4>
 __device__ inline void copy_unaligned(uint8_t* dst, const uint8_t* src, uint32_t len,
                                       const uint8_t* src_end, uint32_t tid, uint32_t nthreads) {
   uint32_t head = (uint32_t)((16u - ((uintptr_t)dst & 15u)) & 15u);
@@ -114,15 +115,15 @@ __device__ inline void copy_unaligned(uint8_t* dst, const uint8_t* src, uint32_t
   const uint8_t* s = src + head;
   const uint32_t sh = (uint32_t)((uintptr_t)s & 3u);
   const uint32_t* sw = reinterpret_cast<const uint32_t*>(s - sh);
-  for (uint32_t k0 = tid; k0 < nw; k0 += 4 * nthreads) {
-    uint4 g[4];
+  for (uint32_t k0 = tid; k0 < nw; k0 += kFlight * nthreads) {
+    uint4 g[kFlight];
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) {
+    for (uint32_t j = 0; j < kFlight; ++j) {
       const uint32_t k = k0 + j * nthreads;
       if (k < nw) g[j] = load_group(sw + 4 * k, sh, src_end);
     }
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) {
+    for (uint32_t j = 0; j < kFlight; ++j) {
       const uint32_t k = k0 + j * nthreads;
       if (k < nw) d4[k] = g[j];
     }
