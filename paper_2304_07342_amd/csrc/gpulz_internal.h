@@ -165,7 +165,8 @@ struct WidthParams {
 
 struct BatchCtrl {
   uint64_t ticket[4];   // next work item of each width's persistent encoder
-  uint64_t T[4];        // work items (chunks) of each width
+  uint64_t T[4];        // work items (chunks) of each width; decoding: [0] those
+                        // of 1- and 2-byte symbols
   uint64_t T_all;       // work items in the batch
   uint64_t slot_total;  // scratch slot bytes used
 };

@@ -263,6 +263,9 @@ __global__ __launch_bounds__(256) void batch_dec_header_kernel(BatchDecArgs a) {
 
 __global__ __launch_bounds__(kPlanThreads) void batch_dec_plan_kernel(BatchDecArgs a) {
   __shared__ uint64_t scratch[kPlanThreads / 64 + 1];
+  __shared__ unsigned long long narrow;  // chunks of 1- and 2-byte symbols
+  if (threadIdx.x == 0) narrow = 0;
+  __syncthreads();
   uint64_t chunk_carry = 0, group_carry = 0, byte_carry = 0;
   for (uint64_t b0 = 0; b0 < a.nbufs; b0 += blockDim.x) {
     const uint64_t b = b0 + threadIdx.x;
@@ -272,6 +275,7 @@ __global__ __launch_bounds__(kPlanThreads) void batch_dec_plan_kernel(BatchDecAr
       if (a.bufs[b].p.status == kOk) {
         n_chunks = a.bufs[b].p.N;
         n_groups = a.bufs[b].groups;
+        if (a.bufs[b].p.S <= 2) atomicAdd(&narrow, (unsigned long long)n_chunks);
       }
     }
     uint64_t t_c, t_g, t_b;
@@ -294,7 +298,10 @@ __global__ __launch_bounds__(kPlanThreads) void batch_dec_plan_kernel(BatchDecAr
       a.bufs[b].p.N = 0;
     }
   }
-  if (threadIdx.x == 0) a.ctrl->T_all = fits ? chunk_carry : 0;
+  if (threadIdx.x == 0) {
+    a.ctrl->T_all = fits ? chunk_carry : 0;
+    a.ctrl->T[0] = narrow;
+  }
 }
 
 __global__ __launch_bounds__(256) void batch_dec_table_kernel(BatchDecArgs a) {
@@ -317,15 +324,8 @@ __global__ __launch_bounds__(256) void batch_dec_table_kernel(BatchDecArgs a) {
     a.out_bytes[b] = sized ? e.p.n : 0;
     a.status[b] = st;
     e.p.status = st;
+    e.p.waves = st == kOk && dec::takes_waves(e.p, a.in_bytes[b], a.ctrl->T[0]);
   }
-}
-
-// Batches of more chunks than this have those of 1- and 2-byte symbols decoded
-// by one wave per chunk: the two decoders and their crossover are those of a
-// single stream (lz_decode.hip has both sides' times).
-constexpr uint64_t kFewBatchChunks = 1536;
-__device__ __forceinline__ bool narrow_by_waves(const BatchDecArgs& a) {
-  return a.ctrl->T_all > kFewBatchChunks;
 }
 
 __global__ __launch_bounds__(dec::kDecThreads, 4) void batch_decode_kernel(BatchDecArgs a) {
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(dec::kDecThreads, 4) void batch_decode_kernel(Batch
   for (uint64_t g = blockIdx.x; g < T; g += gridDim.x) {
     const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].chunk_base; });
     const BatchDecBuf& e = a.bufs[b];
-    if (e.p.status != kOk || (e.p.S <= 2 && narrow_by_waves(a))) continue;
+    if (e.p.status != kOk || e.p.waves) continue;
     const bool ok = dec::decode_stream_chunk_block(
         static_cast<const uint8_t*>(a.in_ptrs[b]), a.in_bytes[b], e.p, a.group_off + e.group_base,
         g - e.chunk_base, static_cast<uint8_t*>(a.out_ptrs[b]), sm);
@@ -346,13 +346,13 @@ constexpr uint32_t kWaveThreads = 1024;
 
 __global__ __launch_bounds__(kWaveThreads, 8) void batch_decode_wave_kernel(BatchDecArgs a) {
   __shared__ __align__(16) uint8_t lds[kWaveThreads / 64 * dec::kWaveLds];
-  if (!narrow_by_waves(a)) return;
+  if (a.ctrl->T[0] <= dec::kFewestForWaves) return;
   const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint64_t T = a.ctrl->T_all, waves = (uint64_t)gridDim.x * (kWaveThreads / 64);
   for (uint64_t g = blockIdx.x + (uint64_t)wave * gridDim.x; g < T; g += waves) {
     const uint64_t b = find_buffer(a.nbufs, g, [&](uint64_t k) { return a.bufs[k].chunk_base; });
     const BatchDecBuf& e = a.bufs[b];
-    if (e.p.status != kOk || e.p.S > 2) continue;
+    if (e.p.status != kOk || !e.p.waves) continue;
     const bool ok = dec::decode_stream_chunk_wave(
         static_cast<const uint8_t*>(a.in_ptrs[b]), a.in_bytes[b], e.p, a.group_off + e.group_base,
         g - e.chunk_base, static_cast<uint8_t*>(a.out_ptrs[b]), lds + wave * dec::kWaveLds);
