@@ -751,14 +751,13 @@ __device__ inline ChunkPlace chunk_place(const uint8_t* in, const DecodeParams& 
 // LDS of one wave of decode_stream_chunk_wave.
 constexpr uint32_t kWaveLds = (sizeof(WaveLds<2>) + 15) / 16 * 16;
 
-// Decode chunk i of a validated stream (of in_bytes bytes) of 1- or 2-byte
-// symbols with one wavefront and kWaveLds bytes of LDS; false (uniformly) if it
-// is corrupt. A record of literals alone is the chunk itself behind its zero
+// Decode chunk i of a validated stream of 1- or 2-byte symbols with one
+// wavefront and kWaveLds bytes of LDS; false (uniformly) if it is corrupt. A record of literals alone is the chunk itself behind its zero
 // flag bytes and is copied (64 MiB of random uint16, C 2048: 49 us; token by
 // token 120).
-__device__ inline bool decode_stream_chunk_wave(const uint8_t* in, uint64_t in_bytes,
-                                                const DecodeParams& p, const uint64_t* group_off,
-                                                uint64_t i, uint8_t* out, uint8_t* lds) {
+__device__ inline bool decode_stream_chunk_wave(const uint8_t* in, const DecodeParams& p,
+                                                const uint64_t* group_off, uint64_t i,
+                                                uint8_t* out, uint8_t* lds) {
   const ChunkPlace k = chunk_place(in, p, group_off, i, out);
   const uint32_t F = k.F, P = k.P, c = k.c;
   if (F == (c + 7) / 8 && P == c * p.S) {
@@ -766,7 +765,7 @@ __device__ inline bool decode_stream_chunk_wave(const uint8_t* in, uint64_t in_b
     uint64_t set = 0;
     for (uint32_t w = lane; 8 * w < F; w += 64) set |= load_bytes8(k.rec, w, F);
     if (!ballot(set != 0)) {
-      stream::copy_unaligned<2>(k.dst, k.rec + F, P, in + in_bytes, lane, 64);
+      stream::copy_unaligned<2>(k.dst, k.rec + F, P, k.rec + F + P, lane, 64);
       return true;
     }
   }

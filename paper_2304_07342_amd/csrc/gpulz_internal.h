@@ -122,6 +122,11 @@ __host__ __device__ constexpr uint64_t decode_max_chunks(uint64_t stream_bytes) 
   return stream_bytes > kHeaderBytes ? (stream_bytes - kHeaderBytes) / 10 : 0;
 }
 
+// Streams (batches: streams together) of fewer bytes than this are decoded by
+// workgroups alone, without a launch of the wave decoder: what it could save
+// them is little, and an empty launch costs about 2 us.
+constexpr uint64_t kWaveStreamBytes = 64 * 1024;
+
 // Record offsets are kept for every 64th chunk (a chunk's own offset is its
 // group's plus a wave prefix sum over the group's table entries).
 __host__ __device__ constexpr uint64_t decode_group_slots(uint64_t stream_bytes) {

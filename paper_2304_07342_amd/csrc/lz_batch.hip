@@ -324,7 +324,8 @@ __global__ __launch_bounds__(256) void batch_dec_table_kernel(BatchDecArgs a) {
     a.out_bytes[b] = sized ? e.p.n : 0;
     a.status[b] = st;
     e.p.status = st;
-    e.p.waves = st == kOk && dec::takes_waves(e.p, a.in_bytes[b], a.ctrl->T[0]);
+    e.p.waves = st == kOk && a.max_total_in_bytes >= kWaveStreamBytes &&
+                dec::takes_waves(e.p, a.in_bytes[b], a.ctrl->T[0]);
   }
 }
 
@@ -354,8 +355,8 @@ __global__ __launch_bounds__(kWaveThreads, 8) void batch_decode_wave_kernel(Batc
     const BatchDecBuf& e = a.bufs[b];
     if (e.p.status != kOk || !e.p.waves) continue;
     const bool ok = dec::decode_stream_chunk_wave(
-        static_cast<const uint8_t*>(a.in_ptrs[b]), a.in_bytes[b], e.p, a.group_off + e.group_base,
-        g - e.chunk_base, static_cast<uint8_t*>(a.out_ptrs[b]), lds + wave * dec::kWaveLds);
+        static_cast<const uint8_t*>(a.in_ptrs[b]), e.p, a.group_off + e.group_base, g - e.chunk_base,
+        static_cast<uint8_t*>(a.out_ptrs[b]), lds + wave * dec::kWaveLds);
     if (!ok && lane_id() == 0) atomicExch(&a.status[b], kCorrupt);
   }
 }
@@ -445,7 +446,7 @@ hipError_t launch_decompress_batch(const BatchDecArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(batch_dec_table_kernel, dim3((uint32_t)a.nbufs), dim3(256), 0, s, a);
   if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(batch_decode_kernel, dim3(device_cus() * 4), dim3(dec::kDecThreads), 0, s, a);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
+  if ((err = hipGetLastError()) != hipSuccess || a.max_total_in_bytes < kWaveStreamBytes) return err;
   hipLaunchKernelGGL(batch_decode_wave_kernel, dim3(device_cus() * 2), dim3(kWaveThreads), 0, s, a);
   return hipGetLastError();
 }

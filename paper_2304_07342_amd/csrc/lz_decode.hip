@@ -5,9 +5,10 @@
 //   decode_kernel          one workgroup of 256 threads per chunk, grid-stride
 //                          over chunks;
 //   decode_wave_kernel     one wavefront per chunk, for streams of 1- and 2-byte
-//                          symbols with many chunks. Both kernels are launched,
-//                          and the one whose turn it is not ends at once: only
-//                          the device knows the stream's header.
+//                          symbols with many chunks. Both kernels are launched
+//                          (streams of some size), and the one whose turn it is
+//                          not ends at once: only the device knows the stream's
+//                          header.
 #include "decode_device.h"
 
 namespace gpulz {
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(kPrepThreads) void decode_prepare_kernel(DecodePrep
       *a.out_bytes = 0;
     } else {
       p.status = a.capacity < p.n ? kOutOfSpace : kOk;
-      p.waves = dec::takes_waves(p, a.in_bytes, p.N);
+      p.waves = a.in_bytes >= kWaveStreamBytes && dec::takes_waves(p, a.in_bytes, p.N);
       *a.out_bytes = p.n;
     }
     *a.params = p;
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(kWaveThreads, 8) void decode_wave_kernel(DecodeArgs
   const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint64_t waves = (uint64_t)gridDim.x * (kWaveThreads / 64);
   for (uint64_t i = blockIdx.x + (uint64_t)wave * gridDim.x; i < p.N; i += waves) {
-    const bool ok = dec::decode_stream_chunk_wave(a.in, a.in_bytes, p, a.group_off, i, a.out,
+    const bool ok = dec::decode_stream_chunk_wave(a.in, p, a.group_off, i, a.out,
                                                   lds + wave * dec::kWaveLds);
     if (!ok && lane_id() == 0) atomicExch(a.status, kCorrupt);
   }
@@ -131,11 +132,10 @@ hipError_t launch_decode_chunks(const DecodeArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(decode_kernel, dim3(kDecodeBlocks), dim3(dec::kDecThreads), 0, s, a);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
+  if (a.in_bytes < kWaveStreamBytes) return hipSuccess;
   // a chunk takes at least 10 stream bytes (table entry, a flag byte and a
-  // payload byte): small streams cannot have the many chunks of the wave
-  // decoder, or not enough for all its workgroups
+  // payload byte): small streams cannot have chunks for all its workgroups
   const uint64_t most = decode_max_chunks(a.in_bytes);
-  if (most <= dec::kFewestForWaves) return hipSuccess;
   constexpr uint32_t kPer = kWaveThreads / 64;
   const uint64_t blocks = (most + kPer - 1) / kPer;
   hipLaunchKernelGGL(decode_wave_kernel, dim3((uint32_t)(blocks < kWaveBlocks ? blocks : kWaveBlocks)),

@@ -188,3 +188,41 @@ def test_batch_with_every_route(q):
     bd.run()
     for (st, y), k in zip(bd.results(), order):
         assert st == gpulz.GPULZ_OK and y.cpu().numpy().tobytes() == want[k]
+
+
+def _kernels(run):
+    """Kernels that a call launches: the nodes of its captured graph."""
+    import ctypes
+    import torch
+    run()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        run()
+    hip = ctypes.CDLL("libamdhip64.so")
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("kind,S,nbytes,most", [("codes", 2, 64 << 10, 2), ("field", 4, 40_000, 2), ("codes", 2, 8 << 20, 3)])
+def test_launches(kind, S, nbytes, most):
+    """A stream (or the streams of a batch) below 64 KiB is decoded without a
+    launch of the wave decoder, which would leave at once."""
+    import torch
+    x = synth.laplace_codes(nbytes // 2, seed=1).view(np.uint8) if S == 2 else synth.uniform_bytes(nbytes, 1)
+    s = gpulz.compress(to_device(x), S, 2048, 128, 2).clone()
+    out = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(gpulz.gpulz_decompress_workspace_size(s.numel()), dtype=torch.uint8, device="cuda")
+    meta = torch.zeros(2, dtype=torch.int64, device="cuda")
+
+    def run():
+        assert gpulz.gpulz_decompress(s.data_ptr(), s.numel(), out.data_ptr(), nbytes, meta.data_ptr(),
+                                      meta.data_ptr() + 8, ws.data_ptr(), ws.numel(),
+                                      torch.cuda.current_stream().cuda_stream) == 0
+    got = _kernels(run)
+    print("decode launches", kind, S, nbytes, s.numel(), got, flush=True)
+    assert got == most
+    assert out.cpu().numpy().tobytes() == x.tobytes()
+    bd = gpulz.BatchDecompressor([s], [nbytes])
+    assert _kernels(bd.run) == most + 2
