@@ -250,7 +250,12 @@ __device__ __forceinline__ void put_record(const uint8_t* src, const uint8_t* in
                                            const uint8_t* slot, uint64_t flag_area, const Sized& z,
                                            uint8_t* table, uint8_t* rec, uint32_t tid,
                                            uint32_t nthreads) {
-  if (tid < 8) table[tid] = (uint8_t)((tid < 4 ? z.F : z.P) >> (8 * (tid & 3u)));
+  // (through values of their own: a choice between the members was compiled as one
+  // between their addresses, for which every workgroup read the launch packet in
+  // host memory: 4 MiB of float32 17.5 us, 4 so)
+  const uint32_t F = z.F, P = z.P;
+  const uint32_t e = tid < 4 ? F : P;
+  if (tid < 8) table[tid] = (uint8_t)(e >> (8 * (tid & 3u)));
   if (z.pointers) {
     stream::copy_bytes(rec, slot, z.F, tid, nthreads);
     stream::copy_bytes(rec + z.F, slot + flag_area, z.P, tid, nthreads);
