@@ -1417,7 +1417,9 @@ __device__ bool build_list(const uint8_t* stage, const uint32_t* hits, uint32_t 
   uint32_t* lkey = list + kEncodeWaves * kListPerWave + wave * kListPerWave;
   uint32_t* cnt = list + 2 * kEncodeWaves * kListPerWave;
   const uint32_t nwords = (c + 31) / 32;
-  const uint32_t w0 = wave * nwords / nwaves, w1 = (wave + 1) * nwords / nwaves;
+  // (waves past the nwaves with a sub-list have an empty share)
+  const uint32_t w0 = min(wave, nwaves) * nwords / nwaves;
+  const uint32_t w1 = min(wave + 1, nwaves) * nwords / nwaves;
   uint32_t n = 0;
   bool over = false;
   for (uint32_t wb = w0; wb < w1; wb += 64) {
@@ -1439,7 +1441,7 @@ __device__ bool build_list(const uint8_t* stage, const uint32_t* hits, uint32_t 
     n += tot;
   }
   wave_sync();
-  if (lane == 0) cnt[wave] = over ? ~0u : n;
+  if (lane == 0 && wave < nwaves) cnt[wave] = over ? ~0u : n;
   if (!over) {
     const T* win = reinterpret_cast<const T*>(stage);
     StreamMatchFor<S, WC> sm;

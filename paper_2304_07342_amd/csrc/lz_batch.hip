@@ -163,7 +163,7 @@ __device__ __forceinline__ void encode_item(const BatchEncArgs& a, uint64_t b, c
     enc::encode_chunk<S, WC>(job, lds);
   } else {
     constexpr uint32_t V = enc::wide::kMaxVectors / (kE == BatchEncoder::kWide16 ? 2 : 1);
-    const enc::wide::Sized z = enc::wide::size_chunk<S, WC, V>(job, lds);
+    const enc::wide::Sized z = enc::wide::size_chunk<S, WC, V, 256, true>(job, lds);
     if (threadIdx.x == 0) {
       job.sizes[0] = z.F;
       job.sizes[1] = z.P;

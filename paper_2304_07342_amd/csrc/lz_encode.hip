@@ -149,11 +149,13 @@ __device__ __forceinline__ uint32_t wide_bytes(uint32_t size) {
 }
 
 
-template <int S, int WC, uint32_t kVectors>
-__global__ __launch_bounds__(enc::wide::kThreads) void wide_size_kernel(FusedArgs a) {
+template <int S, int WC, uint32_t kVectors, uint32_t kThreads>
+__global__ __launch_bounds__(kThreads) void wide_size_kernel(FusedArgs a) {
   extern __shared__ __align__(16) uint8_t lds[];
   const uint64_t i = a.chunk0 + blockIdx.x;
-  const enc::wide::Sized z = enc::wide::size_chunk<S, WC, kVectors>(chunk_job(a, S, i), lds);
+  const enc::wide::Sized z =
+      enc::wide::size_chunk<S, WC, kVectors, kThreads, kThreads == enc::wide::kFewThreads>(
+          chunk_job(a, S, i), lds);
   if (threadIdx.x == 0) wide_view(a).size[i] = z.P | z.F << 16 | (z.pointers ? 1u << 31 : 0u);
 }
 
@@ -204,17 +206,17 @@ __global__ __launch_bounds__(kScanThreads) void wide_scan_kernel(FusedArgs a) {
 
 // kSum: no scan launch came before; every workgroup adds up all sizes itself, and
 // the first writes the header, size and status.
-template <int S, bool kSum>
-__global__ __launch_bounds__(enc::wide::kThreads) void wide_write_kernel(FusedArgs a) {
+template <int S, bool kSum, uint32_t kThreads>
+__global__ __launch_bounds__(kThreads) void wide_write_kernel(FusedArgs a) {
   const WideView w = wide_view(a);
   const uint64_t i = a.chunk0 + blockIdx.x;
   const uint32_t tid = threadIdx.x, lane = lane_id();
   uint64_t off;
   uint32_t own;
   if constexpr (kSum) {
-    __shared__ uint32_t sums[2 * enc::wide::kThreads / 64];
+    __shared__ uint32_t sums[2 * kThreads / 64];
     uint32_t before = 0, all = 0;  // kWideSumChunks records: below 2^31
-    for (uint32_t k = tid; k < a.N; k += enc::wide::kThreads) {
+    for (uint32_t k = tid; k < a.N; k += kThreads) {
       const uint32_t x = wide_bytes(w.size[k]);
       before += k < i ? x : 0u;
       all += x;
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(enc::wide::kThreads) void wide_write_kernel(FusedAr
     off = 0;
     uint64_t total = kHeaderBytes + 8 * a.N;
 #pragma unroll
-    for (uint32_t k = 0; k < enc::wide::kThreads / 64; ++k) {
+    for (uint32_t k = 0; k < kThreads / 64; ++k) {
       off += sums[2 * k];
       total += sums[2 * k + 1];
     }
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(enc::wide::kThreads) void wide_write_kernel(FusedAr
   const enc::wide::Sized z = {own >> 16 & 0x7FFFu, own & 0xFFFFu, own >> 31 != 0};
   enc::wide::put_record(a.in + i * a.C * S, a.in + a.nbytes, a.slots + i * a.slot_bytes,
                         a.flag_area, z, a.out + kHeaderBytes + 8 * i,
-                        a.out + kHeaderBytes + 8 * a.N + off, tid, enc::wide::kThreads);
+                        a.out + kHeaderBytes + 8 * a.N + off, tid, kThreads);
 }
 
 // Policy-1 chunk encoder kernel: one workgroup per chunk.
@@ -349,12 +351,22 @@ bool takes_wide(uint32_t C, uint32_t S, uint32_t MIN, uint32_t policy) {
 namespace {
 template <int S, int WC>
 void launch_size(const FusedArgs& a, hipStream_t s) {
-  const dim3 grid((uint32_t)a.nchunks), block(enc::wide::kThreads);
+  const dim3 grid((uint32_t)a.nchunks);
+  const bool half = a.C * S <= enc::wide::kMaxBytes / 2;
+  constexpr uint32_t kFew = enc::wide::kFewThreads, V = enc::wide::kMaxVectors;
+  if (a.N <= kSpecMaxChunksWide) {
+    const size_t lds = enc::wide::few_area_bytes<S, WC>(a.C) + 4 * enc::wide::kShared;
+    if (half)
+      hipLaunchKernelGGL((wide_size_kernel<S, WC, V * 256 / kFew / 2, kFew>), grid, dim3(kFew), lds, s, a);
+    else
+      hipLaunchKernelGGL((wide_size_kernel<S, WC, V * 256 / kFew, kFew>), grid, dim3(kFew), lds, s, a);
+    return;
+  }
   const size_t lds = enc::wide::lds_bytes(a.C, S, WC);
-  if (a.C * S <= enc::wide::kMaxBytes / 2)
-    hipLaunchKernelGGL((wide_size_kernel<S, WC, enc::wide::kMaxVectors / 2>), grid, block, lds, s, a);
+  if (half)
+    hipLaunchKernelGGL((wide_size_kernel<S, WC, V / 2, 256>), grid, dim3(256), lds, s, a);
   else
-    hipLaunchKernelGGL((wide_size_kernel<S, WC, enc::wide::kMaxVectors>), grid, block, lds, s, a);
+    hipLaunchKernelGGL((wide_size_kernel<S, WC, V, 256>), grid, dim3(256), lds, s, a);
 }
 template <int S>
 hipError_t launch_wide_s(FusedArgs a, hipStream_t s) {
@@ -373,17 +385,17 @@ hipError_t launch_wide_s(FusedArgs a, hipStream_t s) {
       default: launch_size<S, 4>(a, s); break;
     }
   });
+  if (a.N <= kBucketFewChunks && a.C * S > enc::wide::kMaxBytes / 2) {
+    hipLaunchKernelGGL((wide_write_kernel<S, true, 1024>), dim3((uint32_t)a.N), dim3(1024), 0, s, a);
+    return hipGetLastError();
+  }
   if (a.N <= kWideSumChunks) {
-    each([&] {
-      hipLaunchKernelGGL((wide_write_kernel<S, true>), dim3((uint32_t)a.nchunks),
-                         dim3(enc::wide::kThreads), 0, s, a);
-    });
+    hipLaunchKernelGGL((wide_write_kernel<S, true, 256>), dim3((uint32_t)a.N), dim3(256), 0, s, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(wide_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, a);
   each([&] {
-    hipLaunchKernelGGL((wide_write_kernel<S, false>), dim3((uint32_t)a.nchunks),
-                       dim3(enc::wide::kThreads), 0, s, a);
+    hipLaunchKernelGGL((wide_write_kernel<S, false, 256>), dim3((uint32_t)a.nchunks), dim3(256), 0, s, a);
   });
   return hipGetLastError();
 }

@@ -21,24 +21,27 @@ namespace wide {
 // kept (the search decides), so the window does not matter here.
 //
 // 256 MiB float32 field (C 4096, W 256): 508 us with every second position
-// compared with its window in look-back order; 210 us with these sizes (100),
-// the scan (5) and the records written at copy rate (95). 100 MB of float64
-// 104 and 87, 1 MiB 33 and 30. Bound by instruction issue: about 30 vector instructions and 2 LDS accesses per
-// 64 positions (W / 2 vector and as many scalar ones with the window
-// comparison).
-constexpr uint32_t kThreads = 256;
-constexpr uint32_t kMaxVectors = 8;       // 16-byte vectors a thread holds, at most
-constexpr uint32_t kMaxBytes = 16 * kMaxVectors * kThreads;  // largest chunk
+// compared with its window in look-back order; 196 us with these sizes (100),
+// the scan (5) and the records written at copy rate (90). 100 MB of float64 104 and
+// 80, 1 MiB of float32 26 and 10. Bound by
+// instruction issue: about 30 vector instructions and 2 LDS accesses per 64
+// positions (W / 2 vector and as many scalar ones with the window comparison).
+constexpr uint32_t kMaxVectors = 8;       // 16-byte vectors a thread of 256 holds, at most
+constexpr uint32_t kMaxBytes = 16 * kMaxVectors * 256;  // largest chunk
 constexpr uint32_t kBits = 1u << 16;      // first round
 constexpr uint32_t kSmallBits = 1u << 13;  // later rounds
 constexpr uint32_t kListMax = 1024;       // pairs in question after a round
 constexpr uint32_t kKeep = 128;           // candidates handed to the searches
-constexpr uint32_t kShared = 16 + kKeep / 2;  // shared words, then the candidates
+constexpr uint32_t kCounts = 8;           // shared words before a count per wave
+constexpr uint32_t kKeepAt = kCounts + kSpecWaves;
+constexpr uint32_t kShared = kKeepAt + kKeep / 2;  // shared words, then the candidates
 constexpr uint32_t kRepetitive = ~0u;
 
-// LDS: the bitmaps (2 x 8 KiB; after the first round the lists and the small
-// bitmaps lie in the first half), overlaid by the staged chunk with its hit
-// bitmap and candidate list; then the shared words.
+// LDS: the bitmaps of the first round (after it the lists and the small bitmaps
+// lie in the first of them), overlaid by the staged chunk with its hit bitmap
+// and candidate list, or with what the split parse needs; then the shared words.
+// (Bitmaps scaled with C leave more pairs in question: 100 MiB of sorted uint32,
+// C 2048: 96 us, 88 so; 4 MiB, C 256: 38 and 36.)
 __host__ __device__ constexpr uint64_t area_bytes(uint32_t C, uint32_t S, uint32_t wc) {
   const uint64_t e = align_up(encode_lds(C, S, wc, kEncodeWaves), 16), b = 2 * kBits / 8;
   return e > b ? e : b;
@@ -48,6 +51,16 @@ __host__ __device__ constexpr uint64_t lds_bytes(uint32_t C, uint32_t S, uint32_
 }
 __host__ __device__ constexpr bool takes(uint32_t C, uint32_t S, uint32_t MIN) {
   return S >= 4 && MIN >= 2 && (uint64_t)C * S <= kMaxBytes;
+}
+// Launches of few chunks: 16 waves a chunk, and the split parse for chunks of
+// repeating pairs (if it takes chunks of C symbols): 64 chunks of uint32 out of
+// 16 values (C 4096) 1484 us with one wave's parse, 217 so; of a half-zero field
+// 341 and 89.
+constexpr uint32_t kFewThreads = 64 * kSpecWaves;
+template <int S, int WC>
+__host__ __device__ constexpr uint64_t few_area_bytes(uint32_t C) {
+  const uint64_t a = area_bytes(C, S, WC), b = align_up(spec_lds_bytes<S, WC>(C), 16);
+  return C <= kSpecMaxSyms && b > a ? b : a;
 }
 
 // 16-bit hash of the pair (a, b) for round r: 24-bit multiplies (full rate),
@@ -81,8 +94,11 @@ __device__ __forceinline__ bool marked(const uint32_t* twice, uint32_t h) {
 
 // Candidate positions of the chunk at src (c symbols, at most kVectors 16-byte
 // vectors per thread), whole workgroup: their number, with the positions in
-// keep[], or kRepetitive if too many pairs repeat. Uniform.
-template <int S, uint32_t kVectors>
+// keep[], or kRepetitive if too many pairs repeat. Uniform. kRuns: runs of one
+// symbol, which set one bit over and over, one lane after the other, are told
+// from the first vectors: where a quarter of their pairs are such, the chunk is
+// not hashed (256 KiB of uint64 half zero: 68.8 us, 74.4 hashed).
+template <int S, uint32_t kVectors, uint32_t kThreads, bool kRuns>
 __device__ __forceinline__ uint32_t candidates(const uint8_t* src, uint32_t c, uint8_t* area,
                                                uint32_t* shared, uint16_t* keep) {
   using T = typename SymType<S>::T;
@@ -110,7 +126,19 @@ __device__ __forceinline__ uint32_t candidates(const uint8_t* src, uint32_t c, u
   for (uint32_t k = tid; k < 2 * kBits / 128; k += kThreads)
     reinterpret_cast<uint4*>(area)[k] = make_uint4(0, 0, 0, 0);
   if (tid < 4) shared[tid] = 0;
+  if constexpr (kRuns) {
+    uint32_t same = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < V; ++e) same += popc64(ballot(V * tid + e < n && v[0][e] == v[0][e + 1]));
+    if (lane == 0) shared[kCounts + (tid >> 6)] = same;
+  }
   __syncthreads();
+  if constexpr (kRuns) {
+    uint32_t same = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kThreads / 64; ++w) same += shared[kCounts + w];
+    if (n && 4 * uniform(same) >= min(n, V * kThreads)) return kRepetitive;
+  }
   uint32_t hs[kVectors][V / 2];
 #pragma unroll
   for (uint32_t k = 0; k < kVectors; ++k) {
@@ -190,19 +218,53 @@ struct Sized {
   bool pointers;
 };
 
+// Whether a chunk is nearly one long run: fewer than one symbol in 128 differs
+// from the one before it, and the window lets a token cover so many. Its few
+// long tokens are sooner found by one wave than by 16 (zero uint32 symbols, C
+// 4096, W 256: 659 and 828 us; W 32: 356 and 54). Whole workgroup, uniform.
+template <int S, uint32_t kThreads>
+__device__ __forceinline__ bool one_run(const ChunkJob& job, uint32_t* shared) {
+  using T = typename SymType<S>::T;
+  if (job.W <= 128) return false;
+  const T* sym = reinterpret_cast<const T*>(job.src);
+  uint32_t turns = 0;
+  for (uint32_t k = threadIdx.x + 1; k - lane_id() < job.c; k += kThreads)
+    turns += popc64(ballot(k < job.c && sym[k] != sym[k - 1]));
+  if (lane_id() == 0) shared[kCounts + (threadIdx.x >> 6)] = turns;
+  __syncthreads();
+  turns = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kThreads / 64; ++w) turns += shared[kCounts + w];
+  return 128 * uniform(turns) < job.c;
+}
+
 // Sizes one chunk, whole workgroup of kThreads; a record with pointers is written
-// to the chunk's slot, others are their flag zeros and the chunk itself.
-template <int S, int WC, uint32_t kVectors>
-__device__ __forceinline__ Sized size_chunk(const ChunkJob& job, uint8_t* lds) {
+// to the chunk's slot, others are their flag zeros and the chunk itself. The
+// result is wave 0's: once the parse is its work alone the other waves leave.
+// kRuns: see candidates() (streams of many chunks go without: a long one of
+// noisy data pays 3% for it, and one of runs gains nothing).
+template <int S, int WC, uint32_t kVectors, uint32_t kThreads, bool kRuns>
+__device__ __forceinline__ Sized size_chunk(ChunkJob job, uint8_t* lds) {
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr bool kFew = kThreads == kFewThreads;
+  constexpr uint32_t kWaves = kThreads / 64;
   const uint32_t c = job.c;
-  uint32_t* shared = reinterpret_cast<uint32_t*>(lds + area_bytes(job.C, S, WC));
-  uint16_t* keep = reinterpret_cast<uint16_t*>(shared + 16);
+  uint32_t* shared = reinterpret_cast<uint32_t*>(
+      lds + (kFew ? few_area_bytes<S, WC>(job.C) : area_bytes(job.C, S, WC)));
+  uint16_t* keep = reinterpret_cast<uint16_t*>(shared + kKeepAt);
   const Sized literals = {(c + 7) / 8, c * S, false};
-  const uint32_t ncand = candidates<S, kVectors>(job.src, c, lds, shared, keep);
+  const uint32_t ncand = candidates<S, kVectors, kThreads, kRuns>(job.src, c, lds, shared, keep);
   if (ncand == 0) return literals;
   __syncthreads();
+  const bool sampled = ncand == kRepetitive;
+  if constexpr (kFew) {
+    if (sampled && job.C <= kSpecMaxSyms && !one_run<S, kThreads>(job, shared)) {
+      job.sizes = shared;
+      encode_chunk_spec<S, WC, false>(job, lds);
+      return {shared[0], shared[1], true};
+    }
+  }
   uint8_t* stage = lds + pad_bytes<S, WC>();
   uint32_t* hits = reinterpret_cast<uint32_t*>(stage + chunk_lds_bytes(job.C, S));
   const uint32_t nhw = (uint32_t)hit_words(job.C, S);
@@ -210,10 +272,9 @@ __device__ __forceinline__ Sized size_chunk(const ChunkJob& job, uint8_t* lds) {
   stage_chunk<S>(job, stage);
   for (uint32_t k = tid; k < nhw; k += kThreads) hits[k] = 0;
   __syncthreads();
-  const bool sampled = ncand == kRepetitive;
   if (sampled) {  // the window comparison of every second position
     constexpr uint32_t kBlock = Geo<S>::kBlock;
-    build_hits<S, WC>(stage, wave, (c + kBlock - 1) / kBlock, kThreads / 64, job.W, c, true, hits);
+    build_hits<S, WC>(stage, wave, (c + kBlock - 1) / kBlock, kWaves, job.W, c, true, hits);
   } else if (tid < ncand) {
     atomicOr(&hits[keep[tid] >> 5], 1u << (keep[tid] & 31u));
   }
@@ -222,7 +283,8 @@ __device__ __forceinline__ Sized size_chunk(const ChunkJob& job, uint8_t* lds) {
 #pragma unroll
   for (int col = 0; col < WC; ++col) wmask[col] = ballot(64u * col + lane + 1u <= job.W);
   const bool listed = build_list<S, WC>(stage, hits, nhw, sampled, job, wmask, list, wave,
-                                        kThreads / 64);
+                                        kEncodeWaves);
+  if (wave != 0) return literals;
   if (listed) {  // no search found a match: literals only
     const uint32_t* key = list + kEncodeWaves * kListPerWave;
     const uint32_t* cnt = key + kEncodeWaves * kListPerWave;
@@ -231,16 +293,9 @@ __device__ __forceinline__ Sized size_chunk(const ChunkJob& job, uint8_t* lds) {
       any |= lane < cnt[w] && key[w * kListPerWave + lane] != 0;
     if (ballot(any) == 0) return literals;
   }
-  if (wave == 0) {
-    const Parsed r = parse_chunk<S, WC, false>(job, stage, hits, nhw, sampled, false, listed, list,
-                                               wmask, kThreads / 64);
-    if (lane == 0) {
-      shared[0] = r.ntok;
-      shared[1] = r.pay;
-    }
-  }
-  __syncthreads();
-  return {(uniform(shared[0]) + 7) / 8, uniform(shared[1]), true};
+  const Parsed r = parse_chunk<S, WC, false>(job, stage, hits, nhw, sampled, false, listed, list,
+                                             wmask, kEncodeWaves);
+  return {(r.ntok + 7) / 8, r.pay, true};
 }
 
 // Writes a chunk's record, whole workgroup: the table entry, the flag bytes and
