@@ -64,8 +64,11 @@ __host__ __device__ constexpr uint32_t window_blocks(uint32_t W) { return (W + k
 __host__ __device__ constexpr uint32_t row_words(uint32_t nb) { return (kTile / kPB + nb) / 2 + 1; }
 __host__ __device__ constexpr uint32_t max_ins(uint32_t nb) { return kTile + nb * kPB; }
 // The parse takes segments of 2^seg_shift positions, at most one per thread.
+// (1024 threads: 8 positions, so that more waves share the searches at token
+// starts; 256 KiB of runs of up to 8 bytes, C 2048, W 128: 125 us with 16, 74 with
+// 8, 55 with 4; uint16 codes 32.5, 31.2, 35.7.)
 __host__ __device__ constexpr uint32_t seg_shift(uint32_t C, uint32_t threads) {
-  return C <= 16 * threads ? 4u : 5u;
+  return threads == 1024 && C <= 4096 ? 3u : C <= 16 * threads ? 4u : 5u;
 }
 // Position p's result: lanes of the parse read one segment apart, so each
 // segment is followed by one unused word (a bank further each).
@@ -204,7 +207,46 @@ __device__ __forceinline__ bool take_low_bytes(const uint8_t* stage, uint32_t c,
 // uniformly, that a tile's buckets are so full that comparing every position
 // with its window is cheaper (runs of few symbols: kFull) or that most of its
 // positions have the same two bytes (kConstant).
+// A position walks about 2 (nb + 1) candidates for each rank of the mean; of equal
+// share among k hashes, n positions have a mean rank of kPB / 2k. From a mean of
+// 16 / (nb + 1) on the streaming parse is the sooner one where few hashes hold the
+// tile (few symbols) or one holds a third of it, and in launches of few chunks,
+// whose 16 waves share the parse; else the tile is runs of many symbols, where
+// streaming tokens end at their own offset and are searched again. Streaming
+// against buckets, 16 MiB, C 4096, W 256, in us: bytes of 3 values (mean 7) 525 and
+// 695; of 0 and 1, nine zeros of ten (mean 42) 524 and 3409; noise with 7 zero bytes
+// of ten (mean 16) 516 and 1321; runs of up to 64 bytes (mean about 25, 80 hashes)
+// 2308 and 1360; 256 KiB of such runs (C 2048, W 128) 109 and 178. 2-byte symbols
+// always take the streaming parse: with the test in their kernel the compiler
+// orders its loops otherwise, 1-3% slower on codes (128 MiB, C 2048: 1035 and 1052
+// us), for runs 849 us instead of 2390. Above 48 (of at most 63.5) one hash holds
+// nearly all.
 enum SearchEnd { kSearched, kFull, kConstant };
+// Whether few hashes hold the counted tile of n positions, or one a third of it
+// (all waves; uniform; the shared words are free again).
+template <int NT>
+__device__ __forceinline__ bool tile_of_few(const uint32_t* cnt32, uint32_t row, uint32_t n,
+                                            uint32_t* shared) {
+  const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (wave < kHash / 64) {
+    uint32_t sum = 0;
+    for (uint32_t k = 0; k < row; ++k) sum += (cnt32[tid * row + k] & 0xFFFFu) + (cnt32[tid * row + k] >> 16);
+    const uint32_t used = popc64(ballot(sum != 0)), largest = wave_max_u32(sum);
+    if (lane_id() == 0) {
+      shared[2 * wave] = used;
+      shared[2 * wave + 1] = largest;
+    }
+  }
+  __syncthreads();
+  uint32_t hashes = 0, top = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kHash / 64; ++w) {
+    hashes += shared[2 * w];
+    top = max(top, shared[2 * w + 1]);
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(hashes < 32 || 3 * top > n);
+}
 template <int S, int NT>
 __device__ __forceinline__ SearchEnd search(const uint8_t* stage, const uint8_t* sym, bool exact,
                                        uint32_t c, uint32_t W, uint32_t MIN, uint16_t* res,
@@ -245,11 +287,11 @@ __device__ __forceinline__ SearchEnd search(const uint8_t* stage, const uint8_t*
     ranks = readlane(wave_incl_scan(ranks), 63);
     if (lane == 0) atomicAdd(&shared[kMaxWaves], ranks);
     __syncthreads();
-    // n positions of equal share among k buckets of a block have a mean rank of
-    // kPB / 2k: full buckets hold more than about 16 entries per block, and
-    // above 48 (of at most 63.5) one bucket holds nearly all
     ranks = __builtin_amdgcn_readfirstlane(shared[kMaxWaves]);
-    if (ranks > 8 * n) return ranks > 48 * n ? kConstant : kFull;
+    if (__builtin_expect(ranks * (nb + 1) > 16 * n, 0)) {
+      if (S == 2 || NT == 1024 || tile_of_few<NT>(cnt32, row, n, shared))
+        return ranks > 48 * n ? kConstant : kFull;
+    }
     // exclusive scan of the counters, in place: one hash per thread, the
     // hashes with more than 24 entries first, then those with more than 8
     uint32_t wv[kMaxRow], sum = 0;
