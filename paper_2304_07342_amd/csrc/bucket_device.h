@@ -444,12 +444,62 @@ __device__ __forceinline__ uint32_t equal32(const uint8_t* stage, int32_t w,
   return m;
 }
 
+// The walk of position p from slot w on, slot by slot (w = p: none).
+template <int S>
+__device__ __forceinline__ void scan_walk(const typename SymType<S>::T* sym, uint32_t p, uint32_t c,
+                                          uint32_t w, uint32_t& bestL, uint32_t& bestd) {
+  uint32_t b = p, len = 0, off = 0;
+  while (w < p && b < c) {
+    const bool eq = (len < kMaxMatch) & (sym[b] == sym[w]);
+    off = (eq & (len == 0)) ? p - w : off;
+    const bool better = !eq & (len > bestL);
+    bestL = better ? len : bestL;
+    bestd = better ? off : bestd;
+    len = eq ? len + 1 : 0u;
+    b = eq ? b + 1 : p;
+    ++w;
+  }
+  if (len > bestL) {
+    bestL = len;
+    bestd = off;
+  }
+}
+
+// Whether a wave walks a chunk of 1- or 2-byte symbols slot by slot: a block of 64
+// positions in the middle of it (each wave its own) has more slots to take, by a
+// sample of 8 in the middle of their windows, than the masks pay for, but not all
+// (long runs, of which few slots are taken). 8 MiB of bytes, C 4096, W 256: of 2
+// values (8 of 32 slots) 1640 us by the walk, 3140 by masks; nine zeros of ten 1577
+// and 4400; of 3 values (3.6) 1716 and 1990, W 128 1056 and 1031; runs of up to 8
+// (3) 810 and 693. (4- and 8-byte
+// symbols: of 2 values 265 and 289, W 128 199 and 177.)
+template <int S>
+__device__ __forceinline__ bool slots_to_take(const uint8_t* stage, uint32_t c, uint32_t W) {
+  using T = typename SymType<S>::T;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (S >= 4 || W < 32 || c < 1024) return false;
+  const T* sym = reinterpret_cast<const T*>(stage) + c / 2 + 64 * wave + lane_id();
+  const T* y = sym - W / 2 - 8;
+  uint32_t n = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 8; ++e) n += popc64(ballot(y[e] == sym[0] && y[e + 1] == sym[1]));
+  return n > (W > 128 ? 54u : 80u) && n < 480;  // of 64 * 8
+}
+
 // Policy-1 results of every position into res (all waves of NT threads).
 template <int S, int NT>
 __device__ __forceinline__ void scan_search(const uint8_t* stage, uint32_t c, uint32_t W,
                                             uint32_t MIN, uint16_t* res, uint32_t seg_sh) {
   using T = typename SymType<S>::T;
   const T* sym = reinterpret_cast<const T*>(stage);
+  if (slots_to_take<S>(stage, c, W)) {
+    for (uint32_t p = threadIdx.x; p < c; p += NT) {
+      uint32_t bestL = 0, bestd = 0;
+      scan_walk<S>(sym, p, c, p > W ? p - W : 0u, bestL, bestd);
+      res[res_at(p, seg_sh)] = (uint16_t)(bestL >= MIN ? bestL << 8 | (bestd & 0xFFu) : 0u);
+    }
+    return;
+  }
   for (uint32_t p = threadIdx.x; p - lane_id() < c; p += NT) {
     const bool in = p < c;
     const T x = sym[in ? p : 0u];
@@ -466,6 +516,7 @@ __device__ __forceinline__ void scan_search(const uint8_t* stage, uint32_t c, ui
     for (uint32_t k = 0; k < W; k += 32) {
       const int32_t g = w0 + (int32_t)k;  // slot of bit 31
       const uint32_t n = min(32u, W - k);  // slots of this mask
+      if (!ballot(on && cur < g + (int32_t)n)) continue;  // long runs: every lane is past it
       const uint32_t all = equal32<S>(stage, g, x);
       uint32_t m = all;
       if constexpr (S <= 2) m &= equal32<S>(stage, g + 1, x1);
@@ -493,9 +544,21 @@ __device__ __forceinline__ void scan_search(const uint8_t* stage, uint32_t c, ui
         while (m) {
           const int32_t w = g + __builtin_clz(m);
           const uint32_t d = p - (uint32_t)w, lim = min(min(d, kMaxMatch), c - p);
+          // four symbols a step (those past the chunk are slack)
+          const T* a = sym + p + 1;
+          const T* b = sym + w + 1;
           uint32_t L = 1;
-          while (L < lim && sym[p + L] == sym[w + (int32_t)L]) ++L;
-          take(w, d, L);
+          while (L < lim) {
+            uint32_t ne = 0;
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) ne |= (a[e] != b[e] ? 1u : 0u) << e;
+            const uint32_t same = min(first_bit(ne), 4u);
+            L += same;
+            if (same < 4) break;
+            a += 4;
+            b += 4;
+          }
+          take(w, d, min(L, lim));
         }
       } else {
         // runs of four symbols and more wait until every lane has one (or is
@@ -544,7 +607,7 @@ __host__ __device__ constexpr uint64_t scan_lds(uint32_t C, uint32_t S, uint32_t
 }
 // Policy-1 chunks that have room for results and parse in LDS; at MIN = 1 a run
 // of one symbol can win, so no slot may be passed over. 16 MiB of uint16 codes
-// (C 2048, W 128) 865 us slot by slot, 499 so (615 with the one-symbol runs
+// (C 2048, W 128) 865 us slot by slot, 505 so (615 with the one-symbol runs
 // taken as well); 4 MiB of Zipf bytes (W 256) 1825 and 504; a 16 MiB float32
 // field 565 and 126. Bound by vector issue: two instructions a slot and
 // symbol, then the equal slots one by one.
@@ -714,12 +777,23 @@ __device__ __forceinline__ void encode_chunk(const ChunkJob& job, uint8_t* lds) 
     sp.walk(tid < nseg, 0);
     if (tid < nseg) exits[tid] = sp.exit;
     __syncthreads();
-    for (;;) {
-      const uint32_t in = tid && tid < nseg ? exits[tid - 1] : entry;
+    for (uint32_t round = 0;; ++round) {
+      uint32_t in = tid && tid < nseg ? exits[tid - 1] : entry;
       const uint32_t was = sp.exit;
       if (ballot(in != entry)) {
         sp.walk(in != entry, in - sp.first);
         entry = in;
+        // tokens longer than segments settle one segment after the other: after
+        // some rounds a wave settles all of its own in one
+        if (kScan && round >= 4) {
+          for (;;) {
+            const uint32_t up = __shfl_up(sp.exit, 1);
+            if (lane && tid < nseg) in = up;
+            if (!ballot(in != entry)) break;
+            sp.walk(in != entry, in - sp.first);
+            entry = in;
+          }
+        }
       }
       __syncthreads();
       const bool changed = sp.exit != was;

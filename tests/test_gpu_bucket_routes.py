@@ -8,7 +8,7 @@ import oracle
 from gpu_helpers import gpu_compress, gpu_decompress, to_device
 from paper_2304_07342_amd import gpulz, synth
 from test_gpu_bucket import repeats
-from test_gpu_wide_routes import compress_us
+from test_gpu_wide_routes import compress_us, device_us
 
 pytestmark = pytest.mark.gpu
 
@@ -125,3 +125,33 @@ def test_runs_of_many_symbols_stay_in_buckets():
     print("runs us", us, flush=True)
     assert us["runs64"] < 7.2 * us["zipf"]
     assert us["runs8 few"] < 4.3 * us["zipf few"]
+
+
+@pytest.mark.parametrize("S", [1, 2, 4, 8])
+@pytest.mark.parametrize("kind", ["few2", "few3", "zeros70", "zeros90", "zeros100", "runs64", "runs600"])
+def test_scan_of_few_symbols(S, kind):
+    """Policy 1 where many slots are equal: waves that walk slot by slot, groups of
+    slots that every lane has passed, runs extended four symbols a step up to the
+    chunk's end, tokens longer than the parse's segments."""
+    t = {1: np.uint8, 2: np.uint16, 4: np.uint32, 8: np.uint64}[S]
+    for C in (65, 1023, 1024, 2050, 4096):
+        m = 2 * C + C // 3
+        x = one_byte(kind, m, C).astype(t).view(np.uint8)
+        for W, MIN in ((256, 2), (129, 3), (64, 2), (33, 2), (5, 2)):
+            print("scan few", S, kind, C, W, MIN, flush=True)
+            st, s, _, canary = gpu_compress(x, S, C, W, MIN, policy=1)
+            assert st == gpulz.GPULZ_OK and canary and s == oracle.compress(x, S, C, W, MIN, policy=1)
+
+
+def test_scan_time_hardly_depends_on_the_symbols():
+    """Policy 1 walks slot by slot where the masks have too much to take: 4 MiB of
+    bytes, W 256, nine zeros of ten, take 2.2 times the time of Zipf bytes, by masks
+    4.1 times."""
+    us = {}
+    for kind in ("zipf", "zeros90"):
+        x = synth.zipf_text(4 << 20, seed=1).view(np.uint8) if kind == "zipf" else one_byte(kind, 4 << 20, 1)
+        d = to_device(x)[: x.size]
+        c = gpulz.Compressor(x.size, 1, 4096, 256, 2, policy=1)
+        us[kind] = device_us(lambda: c.compress_async(d))
+    print("scan us", us, flush=True)
+    assert us["zeros90"] < 3 * us["zipf"]
