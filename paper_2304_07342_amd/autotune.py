@@ -33,6 +33,12 @@ def candidates(S: int, chunks=CHUNKS, windows=WINDOWS, waves=WAVES):
     return [(C, W, w) for C in chunks if C * S <= MAX_CHUNK_BYTES for W in windows for w in waves]
 
 
+def waves_used(S: int, C: int, min_match: int) -> bool:
+    """Whether the encoder for these parameters runs with the width's waves per
+    chunk; the others have workgroups of their own (gpulz.h, gpulz_compress)."""
+    return min_match == 1 or (C * S > 32 * 1024 if S >= 4 else C > 8192)
+
+
 def measure(sample, S: int, C: int, W: int, min_match: int, waves: int, reps: int = 3):
     """(median ms, ratio) of gpulz_compress on `sample` with these parameters."""
     import torch
@@ -69,8 +75,12 @@ def choose(results, ratio_tol: float):
 
 def tune_width(sample, S: int, min_match: int = 2, ratio_tol: float = 0.02, reps: int = 3,
                cands=None, log=None):
-    results = []
+    results, seen = [], set()
     for C, W, w in (cands or candidates(S)):
+        if not waves_used(S, C, min_match):  # the same kernel for every w
+            if (C, W) in seen:
+                continue
+            seen.add((C, W))
         ms, ratio = measure(sample, S, C, W, min_match, w, reps)
         results.append((C, W, w, ms, ratio))
         if log:
