@@ -1292,19 +1292,17 @@ __device__ __forceinline__ void emit_group(uint32_t cnt, uint32_t desc, uint32_t
   encode_group<S>(cnt, desc, g, win, slot, flag_area, pay);
 }
 
-// Threads tid < nthreads of a workgroup (whole wavefronts): the table entry and,
-// if it ends within the capacity, the record of chunk job.i at offset excl
-// past the table. Slot contents written by another wave have to be visible
-// (a barrier after them). Flag bytes of groups
+// One wavefront: the table entry and, if it ends within the capacity, the
+// record of chunk job.i at offset excl past the table. Flag bytes of groups
 // before g0 are zero and the rest come from the slot; payload bytes before
 // group g0 (64 S per group, all literals) come from the staged chunk in LDS,
 // the rest from the slot. No byte at or past the capacity is written.
 template <int S>
 __device__ inline void write_record(const ChunkJob& job, uint64_t excl, uint32_t F, uint32_t P,
-                                    uint32_t g0, const uint8_t* stage, uint32_t tid = lane_id(),
-                                    uint32_t nthreads = 64) {
+                                    uint32_t g0, const uint8_t* stage) {
+  const uint32_t lane = lane_id();
   const uint64_t te = kHeaderBytes + 8 * job.i;
-  if (tid == 0 && te + 8 <= job.capacity)
+  if (lane == 0 && te + 8 <= job.capacity)
     *reinterpret_cast<uint64_t*>(job.out + te) = (uint64_t)F | ((uint64_t)P << 32);
   const uint64_t base = kHeaderBytes + 8 * job.N;
   if (excl == kDescValue || base + excl + F + P > job.capacity) return;
@@ -1317,11 +1315,11 @@ __device__ inline void write_record(const ChunkJob& job, uint64_t excl, uint32_t
   }
   const uint64_t ge = 8ull * (g0 & ~1u);
   const uint32_t fz = (uint32_t)min<uint64_t>(F, ge);
-  stream::fill_zero(rec, fz, tid, nthreads);
-  if (F > fz) stream::copy_bytes(rec + fz, job.slot + fz, F - fz, tid, nthreads);
+  stream::fill_zero(rec, fz, lane, 64);
+  if (F > fz) stream::copy_bytes(rec + fz, job.slot + fz, F - fz, lane, 64);
   const uint32_t pz = (uint32_t)min<uint64_t>(P, 64ull * S * g0);
-  stream::copy_bytes(rec + F, stage, pz, tid, nthreads);
-  if (P > pz) stream::copy_bytes(rec + F + pz, job.slot + job.flag_area + pz, P - pz, tid, nthreads);
+  stream::copy_bytes(rec + F, stage, pz, lane, 64);
+  if (P > pz) stream::copy_bytes(rec + F + pz, job.slot + job.flag_area + pz, P - pz, lane, 64);
 }
 
 // Where a chunk's record goes: its F flag bytes and its payload (adjacent in
@@ -1637,7 +1635,7 @@ __device__ void encode_chunk(const ChunkJob& job, uint8_t* lds) {
 // ---- the same parse with the chunk split across waves ---------------------
 
 constexpr uint32_t kSpecWaves = 16;      // waves of the split-parse encoder
-constexpr uint32_t kSpecMaxSyms = 4096;  // chunks it takes (16-bit positions)
+constexpr uint32_t kSpecMaxSyms = 4096;  // chunks that launches give it (as a fallback: up to 8192)
 
 __host__ __device__ constexpr uint64_t spec_bitmap_words(uint32_t C) { return (C + 31) / 32 + 2; }
 // LDS: [pad | chunk | hit bitmap | token starts | pointer starts | the same
