@@ -238,11 +238,11 @@ gpulz_status gpulz_decompress_noalloc(const void* d_in, uint64_t in_bytes, void*
  * decompressed by one fixed sequence of launches on one stream (a plan
  * kernel, one persistent kernel per symbol width that takes (buffer, chunk)
  * work items from a device-side ticket, a per-buffer scan, a compaction; to
- * decompress, one kernel by workgroups and one by waves), with no host round
- * trip and no allocation, so the call can be captured in a HIP graph and
- * replayed with new array contents. Each buffer's output is a standalone
- * stream, byte-identical to gpulz_compress / gpulz_decompress on that buffer
- * with the same parameters.
+ * decompress, one kernel by workgroups and, for 64 KiB of streams or more, one
+ * by waves), with no host round trip and no allocation, so the call can be
+ * captured in a HIP graph and replayed with new array contents. Each buffer's
+ * output is a standalone stream, byte-identical to gpulz_compress /
+ * gpulz_decompress on that buffer with the same parameters.
  * All arrays below are device memory holding one entry per buffer.
  */
 

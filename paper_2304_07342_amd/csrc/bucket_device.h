@@ -35,10 +35,10 @@ namespace bucket {
 // best). 16 MiB of 8-bit noise scaled by 256 (C 2048, W 128): 1358 us by low
 // bytes, all alike, 113 by the hash; of byte-swapped codes 331 and 195.
 //
-// Bound by vector instruction issue: about 420 of them per 64 positions, at
-// four fifths of what the SIMDs issue (comparing every position with a window
+// Bound by vector instruction issue: about 420 of them per 64 positions (Zipf
+// bytes), at four fifths of what the SIMDs issue (comparing every position with a window
 // of 256 took over 1000). 64 MiB of Zipf bytes, C 4096, W 256: 2203 us before,
-// 843 so; uint16 codes, C 2048, W 128: 1153 and 536; 1 MiB of codes 56 and 34.
+// 843 so; uint16 codes, C 2048, W 128: 1153 and 536; 1 MiB of codes 56 and 36.
 // Tiles of 1024 positions with 4 waves: tiles of 2048 took 969 us (Zipf), 8
 // waves 958; blocks of 64 positions 917 (shorter runs, twice the counters).
 constexpr uint32_t kPB = 128;         // positions per block
@@ -66,7 +66,8 @@ __host__ __device__ constexpr uint32_t max_ins(uint32_t nb) { return kTile + nb 
 // The parse takes segments of 2^seg_shift positions, at most one per thread.
 // (1024 threads: 8 positions, so that more waves share the searches at token
 // starts; 256 KiB of runs of up to 8 bytes, C 2048, W 128: 125 us with 16, 74 with
-// 8, 55 with 4; uint16 codes 32.5, 31.2, 35.7.)
+// 8, 55 with 4; uint16 codes 32.5, 31.2, 35.7; 1 MiB of these 36.4 with 16, 36.9
+// with 8; 256 KiB of Zipf bytes 23.5 and 21.9.)
 __host__ __device__ constexpr uint32_t seg_shift(uint32_t C, uint32_t threads) {
   return threads == 1024 && C <= 4096 ? 3u : C <= 16 * threads ? 4u : 5u;
 }

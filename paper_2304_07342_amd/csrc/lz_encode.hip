@@ -6,7 +6,7 @@
 //     decoupled look-back and write the table entry and record straight into
 //     the stream;
 //   4- and 8-byte symbols, MIN >= 2, chunks of at most 32 KiB: chunk sizes in
-//     any order, a scan of them, then the records.
+//     any order, a scan of them (many chunks), then the records.
 // The encoders' steps are in bucket_device.h (narrow symbols, policy 1),
 // wide_device.h and encode_device.h (the general ones).
 #include "bucket_device.h"
@@ -141,8 +141,9 @@ __device__ __forceinline__ WideView wide_view(const FusedArgs& a) {
 constexpr uint32_t kWideGroup = 64;
 // Launches of at most this many chunks need no scan launch: every writing
 // workgroup sums the sizes itself. float32 field (C 4096, W 256), without the
-// launch and with it: 256 chunks 38.4 and 42.3 us, 1024 chunks 43.5 and 47.4,
-// 2048 chunks 53.9 and 55.7, 4096 chunks 77.3 and 73.5.
+// launch and with it: 257 chunks 25.3 and 28.7 us, 1024 chunks 31.1 and 34.0,
+// 2048 chunks 42.8 and 44.0, 4096 chunks 68.8 and 66.1; float64 (C 2048, W 32),
+// 2048 chunks 24.2 and 25.7, 4096 chunks 45.6 and 42.9.
 constexpr uint64_t kWideSumChunks = 1024;
 __device__ __forceinline__ uint32_t wide_bytes(uint32_t size) {
   return (size & 0xFFFFu) + (size >> 16 & 0x7FFFu);

@@ -21,11 +21,12 @@ namespace wide {
 // kept (the search decides), so the window does not matter here.
 //
 // 256 MiB float32 field (C 4096, W 256): 508 us with every second position
-// compared with its window in look-back order; 196 us with these sizes (100),
-// the scan (5) and the records written at copy rate (90). 100 MB of float64 104 and
-// 80, 1 MiB of float32 26 and 10. Bound by
-// instruction issue: about 30 vector instructions and 2 LDS accesses per 64
-// positions (W / 2 vector and as many scalar ones with the window comparison).
+// compared with its window in look-back order; 197 us with these sizes (105-117),
+// the scan (5) and the records written at copy rate (88). 100 MB of float64 104 and
+// 77, 1 MiB of float32 26 and 10. A chunk takes 35 vector and 22 scalar
+// instructions and 4.7 LDS accesses, most of them scattered atomics, per 64 positions
+// (W / 2 vector and as many scalar ones with the window comparison); the vector
+// units are busy half the time.
 constexpr uint32_t kMaxVectors = 8;       // 16-byte vectors a thread of 256 holds, at most
 constexpr uint32_t kMaxBytes = 16 * kMaxVectors * 256;  // largest chunk
 constexpr uint32_t kBits = 1u << 16;      // first round
