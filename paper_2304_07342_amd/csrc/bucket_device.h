@@ -66,8 +66,9 @@ __host__ __device__ constexpr uint32_t max_ins(uint32_t nb) { return kTile + nb 
 // The parse takes segments of 2^seg_shift positions, at most one per thread.
 // (1024 threads: 8 positions, so that more waves share the searches at token
 // starts; 256 KiB of runs of up to 8 bytes, C 2048, W 128: 125 us with 16, 74 with
-// 8, 55 with 4; uint16 codes 32.5, 31.2, 35.7; 1 MiB of these 36.4 with 16, 36.9
-// with 8; 256 KiB of Zipf bytes 23.5 and 21.9.)
+// 8, 55 with 4; uint16 codes 32.5, 31.2, 35.7; 256 KiB of Zipf bytes 23.5 and 21.9.
+// 1 MiB of codes goes by its slowest chunk: 35 to 41 us with 16 and 35 to 42 with 8
+// over 16 draws, 37.8 and 37.6 on average.)
 __host__ __device__ constexpr uint32_t seg_shift(uint32_t C, uint32_t threads) {
   return threads == 1024 && C <= 4096 ? 3u : C <= 16 * threads ? 4u : 5u;
 }
